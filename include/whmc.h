@@ -112,7 +112,10 @@ whmc_status whmc_set_stream(whmc_ctx* ctx, void* stream);
  *                              use).  Fewer sites in flight keep their neighbour spinors in the L2
  *                              of their XCD.  FP32 / FP16 kernels and 8-real links are never capped.
  *                              EARG if the device's LDS limits do not allow the value.  Results do
- *                              not depend on it. */
+ *                              not depend on it.
+ * Small lattices take stencil and CG kernels that spread a site's eight directions over a workgroup and
+ * have no such schedule; setting WHMC_OPT_HOP_SCHEDULE or WHMC_OPT_HOP_WG_PER_CU selects the kernels with
+ * one thread per site there too (a hop's bits are the same). */
 #define WHMC_OPT_HOP_SCHEDULE 2
 #define WHMC_OPT_HOP_CHUNK 3
 #define WHMC_OPT_FORCE_KERNEL 4
@@ -127,7 +130,8 @@ whmc_status whmc_get_option(const whmc_ctx* ctx, int option, long long* value);
  * rounds of eight pairs), and keeps the fastest in the context
  * (WHMC_OPT_HOP_SCHEDULE / WHMC_OPT_HOP_CHUNK / WHMC_OPT_HOP_WG_PER_CU, read back with
  * whmc_get_option).  Outputs may be NULL; us receives the time per hop in microseconds.  Uses context
- * scratch of two half fields.  On an error the schedule and cap are left as they were. */
+ * scratch of two half fields.  (On a small lattice, whose hops do not use the schedule, us is the time of
+ * its own kernel.)  On an error the schedule and cap are left as they were. */
 whmc_status whmc_autotune_hop(whmc_ctx* ctx, int* schedule, int* chunk, double* us);
 
 /* Bytes of one field of the given kind in the whmc layout:
@@ -174,7 +178,8 @@ whmc_status whmc_apply_H(whmc_ctx* ctx, void* out, const void* in, int out_parit
  * Allowed: FP64 (18-, 12- or 8-real links) rhs_block = 1 with rhs_lanes = 1, 2 or 4, or rhs_block = 2
  * with rhs_lanes = 1 or 2; FP32 / FP16 (12- or 8-real links) rhs_block = 1, 2 or 4 with
  * rhs_lanes = 1 or 2; other formats WHMC_EUNSUP.  rhs_block = rhs_lanes = 0
- * takes the autotuned blocking and order (rhs_order ignored); one of them 0 reads as 1; anything
+ * takes the autotuned blocking and order (rhs_order ignored), or on small lattices kernels without a
+ * blocking; one of them 0 reads as 1; anything
  * else is WHMC_EARG. */
 whmc_status whmc_apply_H_multi(whmc_ctx* ctx, void* out, const void* in, int out_parity, int dagger, int prec,
                                int links, int nrhs, int rhs_block, int rhs_lanes, int rhs_order);

@@ -172,6 +172,7 @@ __global__ void k_cg_init(CGScalars* sc, const double* rr, double tol2, double d
   sc->done = (*rr == 0.0);
   sc->pause = 0;
   sc->iter = 0;
+  sc->brk = 0;
   sc->alpha = sc->beta = sc->pAp = 0.0;
 }
 
@@ -299,6 +300,8 @@ static whmc_status enqueue_iters(whmc_ctx* c, const Lnk& L, S p, S t, S u, S v, 
 template <class Lnk>
 static whmc_status cg_f64(whmc_ctx* c, double* x, const double* b, double kappa, const whmc_cg_params* prm,
                           whmc_cg_stats* st, Lnk L) {
+  const bool split = split_hops(c, WHMC_F64, prm->links, 1);
+  const double k2 = kappa * kappa;
   Timer tm;
   const size_t hb = (size_t)c->Vh * 192;
   void *r, *p, *t, *u, *v, *te, *to;
@@ -347,7 +350,8 @@ static whmc_status cg_f64(whmc_ctx* c, double* x, const double* b, double kappa,
     while (true) {
       const int n = std::min(check, prm->maxiter - total - pass_iters);
       if (n <= 0) break;
-      WHMC_TRY((enqueue_iters<Lnk, SpinorF64, SpinorF64, false>(c, L, s64(p, Vh), s64(t, Vh), s64(u, Vh),
+      if (split) WHMC_TRY(split_cg(c, WHMC_F64, prm->links, 1, p, t, u, v, r, x, &k2, n));
+      else WHMC_TRY((enqueue_iters<Lnk, SpinorF64, SpinorF64, false>(c, L, s64(p, Vh), s64(t, Vh), s64(u, Vh),
                                                                         s64(v, Vh), s64(r, Vh), s64(x, Vh), kappa, n)));
       WHMC_TRY(read_scalars(c, &hs));
       pass_iters = hs.iter;
@@ -374,6 +378,8 @@ template <class Lnk, class S, class SR>
 static whmc_status cg_mixed(whmc_ctx* c, double* x, const double* b, double kappa, const whmc_cg_params* prm,
                             whmc_cg_stats* st, Lnk L, int sprec, S (*mk)(void*, int), SR (*mkr)(void*, int),
                             int rprec) {
+  const bool split = split_hops(c, sprec, prm->links, 1);
+  const double k2 = kappa * kappa;
   Timer tm;
   const int Vh = c->Vh;
   const size_t hb = (size_t)Vh * 192;
@@ -416,7 +422,8 @@ static whmc_status cg_mixed(whmc_ctx* c, double* x, const double* b, double kapp
   double rel = 1.0;
   while (iters < prm->maxiter) {
     const int n = std::min(check, prm->maxiter - iters);
-    WHMC_TRY((enqueue_iters<Lnk, S, SR, true>(c, L, mk(p, Vh), mk(t, Vh), mk(u, Vh), mk(v, Vh), mkr(rs, Vh),
+    if (split) WHMC_TRY(split_cg(c, sprec, prm->links, 1, p, t, u, v, rs, xs, &k2, n));
+    else WHMC_TRY((enqueue_iters<Lnk, S, SR, true>(c, L, mk(p, Vh), mk(t, Vh), mk(u, Vh), mk(v, Vh), mkr(rs, Vh),
                                               mkr(xs, Vh), kappa, n)));
     WHMC_TRY(read_scalars(c, &hs));
     iters = hs.iter;

@@ -212,6 +212,7 @@ whmc_status hop_full(whmc_ctx* c, int prec, int links, int dag, void* out, const
 whmc_status hop(whmc_ctx* c, int prec, int links, int par, int dag, void* out, const void* in, const void* x,
                 double a, double b, double* norm_out, bool nt_store) {
   WHMC_TRY(ensure_links(c, prec, links));
+  if (!norm_out && split_hops(c, prec, links, 1)) return split_hop(c, prec, links, par, dag, 1, out, in, x, a, b);
   const bool nt = c->stream_links(prec, links);
   if (nt) return hop_nt<true>(c, prec, links, par, dag, out, in, x, a, b, norm_out, nt_store && nt);
   return hop_nt<false>(c, prec, links, par, dag, out, in, x, a, b, norm_out, false);
@@ -607,6 +608,9 @@ whmc_status whmc_create(whmc_ctx** out, const int dims[4], int device, void* str
   c->Vh = (int)(V / 2);
   c->g.Vh = c->Vh;
   c->g.Lxh = dims[3] / 2;
+  c->g.dx = fast_div(c->g.Lxh);
+  c->g.dy = fast_div(dims[2]);
+  c->g.dz = fast_div(dims[1]);
   {
     const long long slice = (long long)dims[1] * dims[2] * dims[3] / 2;
     const bool split = slice % kBlock == 0 && slice / kBlock >= 8;
@@ -628,7 +632,8 @@ whmc_status whmc_create(whmc_ctx** out, const int dims[4], int device, void* str
   if (e == hipSuccess) e = hipMalloc(&c->red.partials, (size_t)maxb * sizeof(double));
   if (e == hipSuccess) e = hipMalloc(&c->red.counter, 64 * sizeof(unsigned));
   if (e == hipSuccess) e = hipMalloc(&c->red.result, 64 * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(&c->scal, kMaxRhs * sizeof(CGScalars));
+  if (e == hipSuccess) e = hipMalloc(&c->scal_base, 2 * kMaxRhs * sizeof(CGScalars));
+  c->scal = c->scal_base;
   if (e == hipSuccess) e = hipHostMalloc(&c->scal_host, kMaxRhs * sizeof(CGScalars), hipHostMallocDefault);
   if (e == hipSuccess) e = hipHostMalloc(&c->host_pinned, 64 * sizeof(double), hipHostMallocDefault);
   if (e == hipSuccess) e = hipMemsetAsync(c->red.counter, 0, 64 * sizeof(unsigned), c->stream);
@@ -662,7 +667,7 @@ void whmc_destroy(whmc_ctx* c) {
   (void)hipFree(c->red.partials);
   (void)hipFree(c->red.counter);
   (void)hipFree(c->red.result);
-  (void)hipFree(c->scal);
+  (void)hipFree(c->scal_base);
   if (c->scal_host) (void)hipHostFree(c->scal_host);
   if (c->host_pinned) (void)hipHostFree(c->host_pinned);
   for (auto& kv : c->ws) (void)hipFree(kv.second.first);
@@ -850,6 +855,8 @@ whmc_status whmc_autotune_hop(whmc_ctx* c, int* schedule, int* chunk, double* us
   WHMC_HIP(hipEventCreate(&e0));
   WHMC_HIP(hipEventCreate(&e1));
   const Geom saved = c->g;
+  const bool saved_off = c->split_off;
+  c->split_off = true;   // the candidates are orders of the one-thread-per-site kernels
   // every candidate is timed in each of kRounds rounds (rounds interleave the candidates, so clock
   // and temperature drifts hit all of them alike) and keeps its best round: the differences between
   // candidates (a few per cent) are below the spread of a single short timing
@@ -873,6 +880,18 @@ whmc_status whmc_autotune_hop(whmc_ctx* c, int* schedule, int* chunk, double* us
         rc = WHMC_EHIP;
       if (rc == WHMC_OK) best_us[q] = std::min(best_us[q], ms * 1e3 / (2.0 * kPairs));
     }
+  c->split_off = saved_off;
+  double split_us = 0.0;
+  if (rc == WHMC_OK && split_hops(c, WHMC_F64, WHMC_L18, 1)) {   // what a hop of this context takes
+    float ms = 0.f;
+    rc = pair();
+    if (rc == WHMC_OK && hipEventRecord(e0, c->stream) != hipSuccess) rc = WHMC_EHIP;
+    for (int rep = 0; rep < kPairs && rc == WHMC_OK; ++rep) rc = pair();
+    if (rc == WHMC_OK && (hipEventRecord(e1, c->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
+                          hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
+      rc = WHMC_EHIP;
+    split_us = ms * 1e3 / (2.0 * kPairs);
+  }
   size_t qbest = 0;
   for (size_t q = 1; q < cand.size(); ++q)
     if (best_us[q] < best_us[qbest]) qbest = q;
@@ -890,7 +909,7 @@ whmc_status whmc_autotune_hop(whmc_ctx* c, int* schedule, int* chunk, double* us
   c->set_wg_cap(pick.cap);
   if (schedule) *schedule = c->g.sched;
   if (chunk) *chunk = c->hop_chunk;
-  if (us) *us = best;
+  if (us) *us = split_us > 0.0 ? split_us : best;
   return WHMC_OK;
 }
 
@@ -919,12 +938,14 @@ whmc_status whmc_set_option(whmc_ctx* c, int option, long long value) {
       WHMC_CHECK(value == 0 || (value >= 2 && value <= 8 && c->set_wg_cap((int)value)), WHMC_EARG,
                  "whmc_set_option: workgroups per compute unit must be 0 (no cap) or 2 .. 8");
       if (value == 0) c->set_wg_cap(0);
+      c->split_off = true;
       return WHMC_OK;
     case WHMC_OPT_HOP_SCHEDULE:
       WHMC_CHECK(value == 0 || value == 1, WHMC_EARG, "whmc_set_option: the schedule must be 0 or 1");
       WHMC_CHECK(c->set_schedule((int)value, c->hop_chunk), WHMC_EARG,
                  "whmc_set_option: the time-slab schedule needs L_t divisible by 8 and time slices of whole "
                  "128-site blocks");
+      c->split_off = true;
       return WHMC_OK;
     default:
       set_error("whmc_set_option: unknown option " + std::to_string(option));

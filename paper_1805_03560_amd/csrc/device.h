@@ -23,6 +23,8 @@
 
 #include <type_traits>
 
+#include "fastdiv.h"
+
 #define WHMC_DEV __device__ __forceinline__
 
 namespace whmc {
@@ -181,6 +183,7 @@ struct Geom {
   int L[4];
   int Vh;
   int Lxh;   // L_x / 2
+  FastDiv dx, dy, dz;   // by Lxh, L_y, L_z
   int nbs;   // blocks per time slice for site_block (0: a slice is not a whole number of blocks)
   int xq;    // workgroups per XCD per time slice, ceil(nbs / 8); 0: plain eighths of the lattice
   // single-RHS stencil schedule (site_block): 0 = slice ranges (site_block_xq); 1 = time slabs:
@@ -195,11 +198,11 @@ struct Coords {
 
 WHMC_DEV Coords coords_of(const Geom& g, int i, int par) {
   Coords c;
-  c.row = i / g.Lxh;
+  c.row = g.dx.div(i);
   c.xh = i - c.row * g.Lxh;
-  int tz = c.row / g.L[2];
+  int tz = g.dy.div(c.row);
   c.y = c.row - tz * g.L[2];
-  c.t = tz / g.L[1];
+  c.t = g.dz.div(tz);
   c.z = tz - c.t * g.L[1];
   c.x = 2 * c.xh + ((par + c.t + c.z + c.y) & 1);
   return c;
@@ -451,6 +454,14 @@ struct SpinorF16 {
     }
   }
 };
+
+// field r of consecutive ones
+WHMC_DEV SpinorF64 field(SpinorF64 s, int r) { return SpinorF64{s.p + (size_t)r * 12 * s.stride, s.stride}; }
+WHMC_DEV SpinorF32 field(SpinorF32 s, int r) { return SpinorF32{s.p + (size_t)r * 6 * s.stride, s.stride}; }
+WHMC_DEV SpinorF16 field(SpinorF16 s, int r) {
+  char* base = (char*)s.p + (size_t)r * 52 * s.stride;
+  return SpinorF16{(uint4*)base, (float*)(base + (size_t)48 * s.stride), s.stride};
+}
 
 // ------------------------------------------------------------------ link storage
 // every link type: load(par, mu, i) -> U_{x,mu} for the site x of parity `par`, cb index i.

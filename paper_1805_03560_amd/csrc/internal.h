@@ -67,6 +67,7 @@ struct CGScalars {
   int pause;        // mixed precision: reliable update requested
   int iter;         // iterations completed
   int active;       // multi-RHS: 1 while the rhs still iterates
+  int brk;          // breakdown seen by the direction-split kernels, turned into `done` by the next step
 };
 
 constexpr int kMaxRhs = 16;
@@ -96,7 +97,10 @@ struct whmc_ctx {
   std::map<std::string, std::pair<int, double>> tuned;   // autotuned multi-RHS blockings (16 nb + lanes, us)
   whmc::Reduce red{};
   void* noalloc_scratch = nullptr;   // device address of the static scratch of whmc_apply_MdagM_noalloc
-  whmc::CGScalars* scal = nullptr;   // kMaxRhs entries
+  // two buffers of kMaxRhs entries: the direction-split CG writes the scalars of the next iteration into
+  // the other one; scal is the current one
+  whmc::CGScalars* scal_base = nullptr;
+  whmc::CGScalars* scal = nullptr;
   whmc::CGScalars* scal_host = nullptr;  // pinned mirror
   double* host_pinned = nullptr;     // small pinned buffer for scalar read-back
   // cache policy: stream (non-temporal) link loads when the link array of a format is larger
@@ -110,6 +114,7 @@ struct whmc_ctx {
   // reserves stencil_lds bytes of LDS it does not use, so that at most hop_wg_per_cu workgroups fit
   // on a compute unit (0 = no cap, stencil_lds = 0).  Fewer sites in flight per XCD keep the
   // neighbour spinors of the sites in flight inside that XCD's L2.
+  bool split_off = false;        // a schedule or cap was asked for: no direction-split kernels
   int hop_wg_per_cu = 0;
   unsigned stencil_lds = 0;
   int lds_per_cu = 0, lds_per_wg = 0;   // device limits, read at creation
@@ -165,6 +170,18 @@ whmc_status gauge_changed(whmc_ctx* c);   // invalidate derived copies after the
 // if norm_out != null the FP64 sum |out|^2 is written there (device pointer).
 whmc_status hop(whmc_ctx* c, int prec, int links, int par, int dag, void* out, const void* in, const void* x,
                 double a, double b, double* norm_out, bool nt_store = false);
+
+// ---- direction-split kernels for small lattices (split.hip)
+bool split_hops(const whmc_ctx* c, int prec, int links, int nrhs);   // whether this call takes them
+whmc_status split_hop(whmc_ctx* c, int prec, int links, int par, int dag, int nrhs, void* out, const void* in,
+                      const void* x, double a, double b);
+// rr_dev[q] = |r_q|^2, r_q = b_q - A(kappa_q) x_q for the right-hand sides q in mask, FP64 with 18-real links
+whmc_status split_residual(whmc_ctx* c, unsigned mask, int nrhs, const double* x, const double* b, const double* k2,
+                           void* t, void* u, void* v, void* r, double* rr_dev);
+// n CG iterations on nrhs right-hand sides (r, x: FP64 with FP64 links, else FP32); the scalars after
+// them are in c->scal
+whmc_status split_cg(whmc_ctx* c, int prec, int links, int nrhs, void* p, void* t, void* u, void* v, void* r, void* x,
+                     const double* k2, int n);
 
 // ---- FP64 BLAS on half fields (core.hip); n = number of half fields
 whmc_status axpby_f64(whmc_ctx* c, double* y, double a, const double* x, double b, int nhalf);  // y = a x + b y

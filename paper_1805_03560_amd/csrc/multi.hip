@@ -25,14 +25,6 @@
 
 namespace whmc {
 
-// ------------------------------------------------------------------ field offsets
-WHMC_DEV SpinorF64 field(SpinorF64 s, int r) { return SpinorF64{s.p + (size_t)r * 12 * s.stride, s.stride}; }
-WHMC_DEV SpinorF32 field(SpinorF32 s, int r) { return SpinorF32{s.p + (size_t)r * 6 * s.stride, s.stride}; }
-WHMC_DEV SpinorF16 field(SpinorF16 s, int r) {
-  char* base = (char*)s.p + (size_t)r * 52 * s.stride;
-  return SpinorF16{(uint4*)base, (float*)(base + (size_t)48 * s.stride), s.stride};
-}
-
 struct K2 {
   double v[kMaxRhs];
 };
@@ -610,6 +602,12 @@ static whmc_status resolve_blocking(whmc_ctx* c, int prec, int links, int nrhs, 
   return WHMC_OK;
 }
 
+// the formats of the multi-RHS kernels
+static bool split_format(int prec, int links) {
+  if (links != WHMC_L18 && links != WHMC_L12 && links != WHMC_L8) return false;
+  return prec == WHMC_F64 || ((prec == WHMC_F32 || prec == WHMC_F16) && links != WHMC_L18);
+}
+
 // ---- masked multi-RHS CG
 struct Timer {
   std::chrono::steady_clock::time_point t0 = std::chrono::steady_clock::now();
@@ -628,6 +626,7 @@ __global__ void k_minit(CGScalars* sc, const double* rr, int n, double tol2, dou
   sc[r].iter = 0;
   sc[r].alpha = sc[r].beta = sc[r].pAp = sc[r].rr_old = 0.0;
   sc[r].active = 1;
+  sc[r].brk = 0;
 }
 
 __global__ void k_mresume(CGScalars* sc, int r, const double* rr, int converged) {
@@ -751,6 +750,7 @@ static void enqueue_residual(whmc_ctx* c, unsigned mask, int nrhs, int order, co
 
 static whmc_status residual_multi(whmc_ctx* c, unsigned mask, int nrhs, const double* x, const double* b,
                                   const K2& k2, void* t, void* u, void* v, void* r64, double* rr_dev) {
+  if (split_hops(c, WHMC_F64, WHMC_L18, nrhs)) return split_residual(c, mask, nrhs, x, b, k2.v, t, u, v, r64, rr_dev);
   Blocking bk;
   WHMC_TRY(autotune_blocking(c, WHMC_F64, WHMC_L18, nrhs, &bk, nullptr));
   const int Vh = c->Vh;
@@ -793,8 +793,11 @@ whmc_status cg_solve_multi(whmc_ctx* c, double* x, const double* b, const double
   const size_t sb = field_bytes(prec, Vh);
   const int rprec = mixed ? WHMC_F32 : WHMC_F64;
   const size_t rb = field_bytes(rprec, Vh);
-  Blocking bk;
-  WHMC_TRY(resolve_blocking(c, prec, links, nrhs, prm->rhs_block, prm->rhs_lanes, prm->rhs_order, &bk));
+  // the direction-split kernels of small lattices, unless the caller asks for a blocking
+  const bool split = prm->rhs_block <= 0 && prm->rhs_lanes <= 0 && split_hops(c, prec, links, nrhs);
+  Blocking bk{1, 1, 0};
+  if (!split)
+    WHMC_TRY(resolve_blocking(c, prec, links, nrhs, prm->rhs_block, prm->rhs_lanes, prm->rhs_order, &bk));
   void *p, *t, *u, *v, *rs, *xs, *r64, *ft, *fu, *fv;
   WHMC_TRY(workspace(c, "m_p", sb * nrhs, &p));
   WHMC_TRY(workspace(c, "m_t", sb * nrhs, &t));
@@ -846,7 +849,8 @@ whmc_status cg_solve_multi(whmc_ctx* c, double* x, const double* b, const double
   for (int pass = 0; pass < 4 && !all; ++pass) {
     int max_iter_seen = 0;
     while (true) {
-      WHMC_TRY(with_format(c, prec, links, stream_multi(c, prec, links, nrhs, bk), [&](auto L, auto mk) {
+      if (split) WHMC_TRY(split_cg(c, prec, links, nrhs, p, t, u, v, rs, xs, k2.v, check));
+      else WHMC_TRY(with_format(c, prec, links, stream_multi(c, prec, links, nrhs, bk), [&](auto L, auto mk) {
         return with_blocking<decltype(L)>(bk, [&](auto nbc, auto lanes) {
           constexpr int NB = decltype(nbc)::value, R = decltype(lanes)::value;
           // FP64 links run the plain FP64 CG, low-precision links the mixed one
@@ -976,6 +980,8 @@ extern "C" whmc_status whmc_apply_H_multi(whmc_ctx* c, void* out, const void* in
   WHMC_CHECK(c && out && in && out != in, WHMC_EARG, "whmc_apply_H_multi: bad pointers");
   WHMC_CHECK(out_parity == 0 || out_parity == 1, WHMC_EARG, "whmc_apply_H_multi: out_parity must be 0 or 1");
   WHMC_CHECK(nrhs >= 1 && nrhs <= kMaxRhs, WHMC_EARG, "whmc_apply_H_multi: nrhs must be in [1, 16]");
+  if (rhs_block <= 0 && rhs_lanes <= 0 && split_format(prec, links) && split_hops(c, prec, links, nrhs))
+    return split_hop(c, prec, links, out_parity, dagger ? 1 : 0, nrhs, out, in, nullptr, 0.0, 1.0);
   Blocking b;
   WHMC_TRY(resolve_blocking(c, prec, links, nrhs, rhs_block, rhs_lanes, rhs_order, &b));
   return mhop(c, prec, links, out_parity, dagger ? 1 : 0, nrhs, b, out, in);

@@ -1,0 +1,424 @@
+// The even/odd stencil and the CG iteration on lattices too small to fill the chip with one thread
+// per output site: the eight hops into a site are eight wavefronts of one workgroup.
+//
+// A workgroup of 512 threads holds 64 output sites of one right-hand side.  Wavefront d = 2 mu + (0
+// forward, 1 backward) loads the neighbour spinor and the link of its direction for all 64 sites,
+// projects and multiplies (hop_half, the same arithmetic as the one-thread-per-site kernels) and puts
+// the resulting half spinor into LDS; then every thread sums two of a site's twelve components over
+// the eight directions, in the order of the one-thread kernels, and does that pair's share of the
+// epilogue.  A hop is then one memory round trip and one barrier deep instead of eight dependent
+// direction steps, and 12^3 x 24 (20736 output sites) gives 2592 wavefronts to the 1024 SIMDs
+// instead of 324.  The results of a hop are bit for bit those of the other stencil kernels.
+//
+// The sums of a CG iteration need no kernels of their own here: the workgroups of the step that uses a
+// sum add up the few partial sums themselves, all in the same order, so an iteration is five launches
+// instead of seven.  What bounds it: at 8^4 the five launches (about 6 us each with their wait for
+// the previous one); at 12^3x24 FP64 the links and spinors, which every kernel reads anew from the
+// Infinity Cache (an XCD's L2 starts a kernel empty: 31 MB counted per hop, 6.7 us, 5.2 TB/s); in FP16
+// the arithmetic and address instructions of a wavefront (about 400).
+#include <type_traits>
+
+#include "internal.h"
+#include "stencil.h"
+
+namespace whmc {
+
+constexpr int kSplitSites = 64, kSplitWG = 512;
+// LDS row of a component: 64 sites and 4 entries of padding, so that the two component pairs that
+// lanes 0..7 and 8..15 read in one cycle (F32) fall into different banks
+constexpr int kSplitRow = kSplitSites + 4;
+
+// ------------------------------------------------------------------ two components of a site
+// pair q (0..5) is components 2q and 2q + 1 in every storage format
+WHMC_DEV void load2(const SpinorF64& f, int i, int q, cplx<double>* v) {
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const double2 w = f.p[aos(2 * q + j, i, 12, f.stride)];
+    v[j] = {w.x, w.y};
+  }
+}
+WHMC_DEV void load2(const SpinorF32& f, int i, int q, cplx<float>* v) {
+  const float4 w = f.p[aos(q, i, 6, f.stride)];
+  v[0] = {w.x, w.y};
+  v[1] = {w.z, w.w};
+}
+WHMC_DEV void load2(const SpinorF16& f, int i, int q, cplx<float>* v) {
+  const uint2 w = ((const uint2*)(f.p + aos(q >> 1, i, 3, f.stride)))[q & 1];
+  const float sc = f.scale[i];
+  v[0] = {sc * h2f((unsigned short)(w.x & 0xffffu)), sc * h2f((unsigned short)(w.x >> 16))};
+  v[1] = {sc * h2f((unsigned short)(w.y & 0xffffu)), sc * h2f((unsigned short)(w.y >> 16))};
+}
+// called by all 64 lanes of a wavefront (lane = 8 q + site % 8); only active lanes store
+WHMC_DEV void store2(const SpinorF64& f, int i, int q, bool act, const cplx<double>* v) {
+  if (!act) return;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) f.p[aos(2 * q + j, i, 12, f.stride)] = make_double2(v[j].re, v[j].im);
+}
+WHMC_DEV void store2(const SpinorF32& f, int i, int q, bool act, const cplx<float>* v) {
+  if (act) f.p[aos(q, i, 6, f.stride)] = make_float4(v[0].re, v[0].im, v[1].re, v[1].im);
+}
+WHMC_DEV void store2(const SpinorF16& f, int i, int q, bool act, const cplx<float>* v) {
+  float m = act ? fmaxf(fmaxf(fabsf(v[0].re), fabsf(v[0].im)), fmaxf(fabsf(v[1].re), fabsf(v[1].im))) : 0.f;
+#pragma unroll
+  for (int off = 8; off < 64; off <<= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  if (!act) return;
+  const float inv = m > 0.f ? 1.0f / m : 0.f;
+  if (q == 0) f.scale[i] = m;
+  uint2 w;
+  w.x = (unsigned int)f2h(inv * v[0].re) | ((unsigned int)f2h(inv * v[0].im) << 16);
+  w.y = (unsigned int)f2h(inv * v[1].re) | ((unsigned int)f2h(inv * v[1].im) << 16);
+  ((uint2*)(f.p + aos(q >> 1, i, 3, f.stride)))[q & 1] = w;
+}
+
+// sum over the eight directions of components 2q, 2q + 1 of the site in column s (accumulate())
+template <int DAG, typename R>
+WHMC_DEV void gather2(const cplx<R> (*u)[6][kSplitRow], int q, int s, cplx<R>* acc) {
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int k = 2 * q + j, sp = k / 3;
+    const bool up = k < 6;
+    const int same = up ? k : k - 6;                        // spin s - 2 of the half spinor
+    const int swap = up ? k : (3 - sp) * 3 + (k - 3 * sp);  // the other spin
+    cplx<R> a = {R(0), R(0)};
+#pragma unroll
+    for (int d = 0; d < 8; ++d) {
+      const int mu = d >> 1;
+      const R sg = ((d & 1) == 0) == (DAG != 0) ? R(1) : R(-1);
+      const cplx<R> v = u[d][mu == 0 || mu == 3 ? same : swap][s];
+      const R f = up ? R(1) : (mu >= 2 && sp == 3 ? -sg : sg);
+      const bool rot = (mu & 1) && !up;   // times i
+      a.re += f * (rot ? -v.im : v.re);
+      a.im += f * (rot ? v.re : v.im);
+    }
+    acc[j] = a;
+  }
+}
+
+// sum over the workgroup in a fixed order, valid in every thread after the barrier in between
+WHMC_DEV void wave_total(double v, double* lds) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+}
+WHMC_DEV double add_waves(const double* lds) {
+  double s = 0.0;
+#pragma unroll
+  for (int w = 0; w < kSplitWG / 64; ++w) s += lds[w];
+  return s;
+}
+// this thread's share of one rhs's partial sums
+WHMC_DEV double my_partials(const double* p, int n) {
+  double t = 0.0;
+  for (int k = threadIdx.x; k < n; k += kSplitWG) t += p[k];
+  return t;
+}
+
+struct SplitK2 {
+  double v[kMaxRhs];
+};
+
+// keeps the loads of these kernel arguments above the first branch, so that they wait for memory once
+// together instead of once per branch
+WHMC_DEV void pin(const Geom& g, const void* links, const void* in) {
+  asm volatile("" ::"s"(g.L[0]), "s"(g.L[1]), "s"(g.L[2]), "s"(g.L[3]), "s"(g.Vh), "s"(g.Lxh), "s"(g.dx.m), "s"(g.dx.sh),
+               "s"(g.dy.m), "s"(g.dy.sh), "s"(g.dz.m), "s"(g.dz.sh), "s"(links), "s"(in));
+}
+
+// ------------------------------------------------------------------ kernels
+enum { kPlain, kXpay, kCgHop, kCgU, kCgR, kRes };
+
+// MODE kPlain: out = b H in;  kXpay: out = a x + b H in;  and the steps of a CG iteration, which skip a
+// stopped right-hand side:  kCgHop: out = H in;  kCgU: out = x - k2 H in, |out|^2 to part_out;
+// kCgR: with (p, A p) from part_in, alpha = |r|^2 / (p, A p), A p = x - k2 H in, r -= alpha A p,
+// xs += alpha p, |r|^2 to part_out.  kRes: out = p - (x - k2 H in), |out|^2 to part_out (the last hop of a
+// residual).  The steps after kXpay work on the right-hand sides of the set `mask` that are not stopped
+// (sc may be null: none is).
+template <int DAG, int MODE, class Lnk, class S, class SR>
+__global__ __launch_bounds__(kSplitWG) void k_split(FastDiv by_nrhs, int nrhs, unsigned mask, CGScalars* sc, Geom g, int par,
+                                                    Lnk L, S in0, S x0, S out0, S p0, SR r0, SR xs0, double a, double b,
+                                                    const double* part_in, double* part_out, int nb, SplitK2 k2) {
+  using R = typename S::Real;
+  using RR = typename SR::Real;
+  constexpr bool cg = MODE >= kCgHop;
+  const int B = xcd_remap(blockIdx.x, gridDim.x);   // the right-hand sides of a block run back to back
+  const int sb = by_nrhs.div(B), r = B - sb * nrhs;
+  pin(g, L.p, in0.p);
+  // scalars of the epilogue, read now so that their latency overlaps the hop
+  const R kk = MODE == kCgU || MODE == kCgR || MODE == kRes ? R(k2.v[r]) : R(0);
+  const double rr_cur = MODE == kCgR ? sc[r].rr : 0.0;
+  if (cg && (!((mask >> r) & 1u) || (sc && (sc[r].done | sc[r].pause)))) return;
+  __shared__ cplx<R> lds[8][6][kSplitRow];
+  __shared__ double lred[kSplitWG / 64], lsum[kSplitWG / 64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const double part = MODE == kCgR ? my_partials(part_in + (size_t)r * nb, nb) : 0.0;
+  const int i = sb * kSplitSites + lane;
+  // the thread's component pair in the second half: pair q of the wavefront's eight sites
+  const int q = lane >> 3, s2 = wave * 8 + (lane & 7), i2 = sb * kSplitSites + s2;
+  const bool act = q < 6 && i2 < g.Vh;
+  cplx<R> xv[2], pv[2];
+  cplx<RR> rv[2], xsv[2];
+  if (i < g.Vh) {
+    const Coords c = coords_of(g, i, par);
+    const S in = field(in0, r);
+    HalfSpinor<R> u;
+    switch (wave) {
+      case 0: hop_half<0, +1, DAG>(g, c, par, i, L, in, u); break;
+      case 1: hop_half<0, -1, DAG>(g, c, par, i, L, in, u); break;
+      case 2: hop_half<1, +1, DAG>(g, c, par, i, L, in, u); break;
+      case 3: hop_half<1, -1, DAG>(g, c, par, i, L, in, u); break;
+      case 4: hop_half<2, +1, DAG>(g, c, par, i, L, in, u); break;
+      case 5: hop_half<2, -1, DAG>(g, c, par, i, L, in, u); break;
+      case 6: hop_half<3, +1, DAG>(g, c, par, i, L, in, u); break;
+      default: hop_half<3, -1, DAG>(g, c, par, i, L, in, u); break;
+    }
+#pragma unroll
+    for (int k = 0; k < 6; ++k) lds[wave][k][lane] = u.c[k / 3][k % 3];
+  }
+  // the epilogue's vectors, on their way while the workgroup meets (before the hop they would hold its
+  // registers: 142 VGPRs in FP64, one
+  // workgroup per compute unit: 14.1 against 11.3 us for the last step at 12^3x24)
+  if (MODE != kPlain && MODE != kCgHop && act) load2(field(x0, r), i2, q, xv);
+  if ((MODE == kCgR || MODE == kRes) && act) load2(field(p0, r), i2, q, pv);
+  if (MODE == kCgR && act) {
+    load2(field(r0, r), i2, q, rv);
+    load2(field(xs0, r), i2, q, xsv);
+  }
+  if (MODE == kCgR) wave_total(part, lsum);
+  __syncthreads();
+  double nrm = 0.0;
+  cplx<R> acc[2];
+  if (act) gather2<DAG>(lds, q, s2, acc);
+  if (MODE == kCgR) {
+    const double pAp = add_waves(lsum);
+    const bool ok = pAp > 0.0 && pAp < INFINITY;   // else a breakdown: p = 0 or not finite
+    const double alpha = ok ? rr_cur / pAp : 0.0;
+    if (sb == 0 && threadIdx.x == 0) {   // fields that nothing else in this launch reads
+      sc[r].pAp = pAp;
+      sc[r].alpha = alpha;
+      sc[r].brk = !ok;
+    }
+    if (act && ok) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const cplx<R> ap = xv[j] - kk * acc[j];
+        rv[j].re -= RR(alpha) * RR(ap.re);
+        rv[j].im -= RR(alpha) * RR(ap.im);
+        xsv[j].re += RR(alpha) * RR(pv[j].re);
+        xsv[j].im += RR(alpha) * RR(pv[j].im);
+      }
+      nrm = double(norm2(rv[0]) + norm2(rv[1]));
+    }
+    store2(field(r0, r), i2, q, act && ok, rv);
+    store2(field(xs0, r), i2, q, act && ok, xsv);
+  } else {
+    if (act) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        if (MODE == kPlain) acc[j] = R(b) * acc[j];
+        if (MODE == kXpay) acc[j] = R(a) * xv[j] + R(b) * acc[j];
+        if (MODE == kCgU) acc[j] = xv[j] - kk * acc[j];
+        if (MODE == kRes) acc[j] = pv[j] - (xv[j] - kk * acc[j]);
+      }
+      if (MODE == kCgU || MODE == kRes) nrm = double(norm2(acc[0]) + norm2(acc[1]));
+    }
+    store2(field(out0, r), i2, q, act, acc);
+  }
+  if (MODE == kCgU || MODE == kCgR || MODE == kRes) {
+    wave_total(nrm, lred);
+    __syncthreads();
+    if (threadIdx.x == 0) part_out[(size_t)r * nb + sb] = add_waves(lred);
+  }
+}
+
+// p = r + beta p, beta = |r|^2 / |r_old|^2 from the partial sums; every workgroup adds them up in the
+// same order, the first one of a rhs writes the scalars of the next iteration into the other buffer
+template <bool MIXED, class S, class SR>
+__global__ __launch_bounds__(kSplitWG) void k_split_p(FastDiv by_nrhs, int nrhs, int Vh, S p0, SR r0, const CGScalars* cur,
+                                                      CGScalars* nxt, const double* part, int nb) {
+  using R = typename S::Real;
+  const int B = xcd_remap(blockIdx.x, gridDim.x);
+  const int sb = by_nrhs.div(B), r = B - sb * nrhs;
+  const bool first = sb == 0 && threadIdx.x == 0;
+  const CGScalars* o = cur + r;
+  const double old_rr = o->rr, stop_rr = o->stop_rr, delta2 = o->delta2, old_rmax2 = o->rmax2;
+  const int halt = o->done | o->pause | o->brk;
+  if (halt) {
+    if (first) {
+      CGScalars* n = nxt + r;
+      n->rr = old_rr, n->pAp = o->pAp, n->alpha = o->alpha, n->beta = o->beta, n->rr_old = o->rr_old;
+      n->stop_rr = stop_rr, n->rmax2 = old_rmax2, n->delta2 = delta2;
+      n->done = o->done | o->brk, n->pause = o->pause, n->iter = o->iter, n->active = o->active, n->brk = 0;
+    }
+    return;
+  }
+  const int lane = threadIdx.x & 63, q = lane >> 3, i = sb * kSplitSites + (threadIdx.x >> 6) * 8 + (lane & 7);
+  const bool act = q < 6 && i < Vh;
+  cplx<R> pv[2];
+  cplx<typename SR::Real> rv[2];
+  if (act) {
+    load2(field(p0, r), i, q, pv);
+    load2(field(r0, r), i, q, rv);
+  }
+  __shared__ double lsum[kSplitWG / 64];
+  wave_total(my_partials(part + (size_t)r * nb, nb), lsum);
+  __syncthreads();
+  const double rr = add_waves(lsum);
+  const double beta = rr / old_rr;
+  const double rmax2 = fmax(old_rmax2, rr);
+  const bool finite = rr < INFINITY;
+  const bool pause = MIXED && finite && (rr <= stop_rr || rr < delta2 * rmax2);
+  const bool done = !finite || (!MIXED && rr <= stop_rr);
+  if (first) {
+    CGScalars* n = nxt + r;
+    n->rr = rr, n->pAp = o->pAp, n->alpha = o->alpha, n->beta = beta, n->rr_old = old_rr;
+    n->stop_rr = stop_rr, n->rmax2 = MIXED && finite ? rmax2 : old_rmax2, n->delta2 = delta2;
+    n->done = done, n->pause = pause, n->iter = o->iter + 1, n->active = o->active, n->brk = 0;
+  }
+  if (pause || done) return;
+  if (act) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      pv[j].re = R(rv[j].re) + R(beta) * pv[j].re;
+      pv[j].im = R(rv[j].im) + R(beta) * pv[j].im;
+    }
+  }
+  store2(field(p0, r), i, q, act, pv);
+}
+
+// ------------------------------------------------------------------ host side
+static SpinorF64 f64(const void* p, int Vh) { return SpinorF64{(double2*)p, Vh}; }
+static SpinorF32 f32(const void* p, int Vh) { return SpinorF32{(float4*)p, Vh}; }
+static SpinorF16 f16(const void* p, int Vh) {
+  return SpinorF16{(uint4*)p, p ? (float*)((uint4*)p + (size_t)3 * Vh) : nullptr, Vh};
+}
+
+// f(link accessor, spinor maker) for a format; the links are cached, never streamed, on these lattices
+template <class F>
+static whmc_status with_links(whmc_ctx* c, int prec, int links, F&& f) {
+  WHMC_TRY(ensure_links(c, prec, links));
+  const int Vh = c->Vh;
+  if (prec == WHMC_F64) {
+    if (links == WHMC_L18) return f(LinkF64_18T<false>{c->U18, Vh}, f64);
+    if (links == WHMC_L12) return f(LinkF64_12T<false>{c->U12, Vh}, f64);
+    return f(LinkF64_8T<false>{c->U8, Vh}, f64);
+  }
+  if (prec == WHMC_F32) {
+    if (links == WHMC_L18) return f(LinkF32_18T<false>{c->U32_18, Vh}, f32);
+    if (links == WHMC_L12) return f(LinkF32_12T<false>{c->U32_12, Vh}, f32);
+    return f(LinkF32_8T<false>{c->U32_8, Vh}, f32);
+  }
+  if (links == WHMC_L12) return f(LinkF16_12T<false>{c->U16_12, Vh}, f16);
+  return f(LinkF16_8T<false>{c->U16_8, Vh}, f16);
+}
+
+static int split_blocks(const whmc_ctx* c) { return (c->Vh + kSplitSites - 1) / kSplitSites; }
+
+// Which calls take these kernels: lattices whose one-thread-per-site grid leaves SIMDs idle or with a
+// single wavefront, as long as the workgroups are few enough that reading a link once per right-hand side
+// (from L2) and the spinors of a 64-site block without the 128-site slice schedule costs less than the
+// idle SIMDs.  us per CG iteration, one thread per site -> split: 8^4 FP64 39.6 -> 30.7, 12^3x24 FP64
+// 52.5 -> 42.8, two rhs FP32 58.1 -> 45.2 and FP16 63.1 -> 48.4, 16^3x32 two rhs FP64 162 -> 144,
+// 16^3x20x40 two rhs FP32 147 -> 126; beyond the lines: 16^3x32 two rhs FP16 81 -> 84, 12-rhs hops at
+// 16^3x32 FP64 129 -> 139 and FP16 39 -> 53, 20^3x40 one rhs FP64 250 -> 271.  FP16 has the least work
+// per site, so its line lies at a total of output sites; FP64 and FP32 have one for the lattice and FP64
+// one for the total.  A schedule or cap that the caller sets selects the one-thread-per-site kernels,
+// which it is about, and so do streamed links.
+bool split_hops(const whmc_ctx* c, int prec, int links, int nrhs) {
+  if (c->split_off || c->stream_links(prec, links)) return false;
+  const long long total = (long long)c->Vh * nrhs;
+  if (prec == WHMC_F16) return total <= 98304;
+  return c->Vh <= 131072 && (prec == WHMC_F32 || total <= 524288);
+}
+
+template <int DAG, int MODE, class Lnk, class S, class SR>
+static void launch_split(whmc_ctx* c, int par, int nrhs, const Lnk& L, S in, S x, S out, S p, SR r, SR xs, double a,
+                         double b, const SplitK2& k2, unsigned mask, CGScalars* sc, const double* part_in,
+                         double* part_out) {
+  const int nb = split_blocks(c);
+  hipLaunchKernelGGL((k_split<DAG, MODE, Lnk, S, SR>), dim3(nb * nrhs), dim3(kSplitWG), 0, c->stream, fast_div(nrhs),
+                     nrhs, mask, sc, c->g, par, L, in, x, out, p, r, xs, a, b, part_in, part_out, nb, k2);
+}
+
+whmc_status split_hop(whmc_ctx* c, int prec, int links, int par, int dag, int nrhs, void* out, const void* in,
+                      const void* x, double a, double b) {
+  auto run = [&](auto L, auto mk) {
+    const auto I = mk(in, c->Vh), X = mk(x, c->Vh), O = mk(out, c->Vh);
+    auto go = [&](auto dagc, auto mode) {
+      launch_split<decltype(dagc)::value, decltype(mode)::value>(c, par, nrhs, L, I, X, O, X, X, X, a, b, SplitK2{}, 0u,
+                                                                 nullptr, nullptr, nullptr);
+    };
+    using D0 = std::integral_constant<int, 0>;
+    using D1 = std::integral_constant<int, 1>;
+    using Plain = std::integral_constant<int, kPlain>;
+    using Xpay = std::integral_constant<int, kXpay>;
+    if (x) dag ? go(D1{}, Xpay{}) : go(D0{}, Xpay{});
+    else dag ? go(D1{}, Plain{}) : go(D0{}, Plain{});
+    return WHMC_OK;
+  };
+  WHMC_TRY(with_links(c, prec, links, run));
+  WHMC_HIP(hipGetLastError());
+  return WHMC_OK;
+}
+
+// sum of nb partials of each rhs in mask, one workgroup per rhs
+__global__ __launch_bounds__(256) void k_split_sum(unsigned mask, const double* part, int nb, double* out) {
+  const int r = blockIdx.x;
+  if (!((mask >> r) & 1u)) return;
+  const double t = sum_partials<256>(part + (size_t)r * nb, nb);
+  if (threadIdx.x == 0) out[r] = t;
+}
+
+whmc_status split_residual(whmc_ctx* c, unsigned mask, int nrhs, const double* x, const double* b, const double* k2,
+                           void* t, void* u, void* v, void* r, double* rr_dev) {
+  SplitK2 kk{};
+  for (int q = 0; q < nrhs; ++q) kk.v[q] = k2[q];
+  const int Vh = c->Vh;
+  const LinkF64_18T<false> L{c->U18, Vh};
+  const SpinorF64 X = f64(x, Vh), B = f64(b, Vh), T = f64(t, Vh), U = f64(u, Vh), V = f64(v, Vh), R = f64(r, Vh);
+  double* pa = c->red.partials;
+  launch_split<0, kCgHop>(c, 0, nrhs, L, X, X, T, X, R, R, 0.0, 0.0, kk, mask, nullptr, pa, pa);
+  launch_split<0, kCgU>(c, 1, nrhs, L, T, X, U, X, R, R, 0.0, 0.0, kk, mask, nullptr, pa, pa);
+  launch_split<1, kCgHop>(c, 0, nrhs, L, U, U, V, U, R, R, 0.0, 0.0, kk, mask, nullptr, pa, pa);
+  launch_split<1, kRes>(c, 1, nrhs, L, V, U, R, B, R, R, 0.0, 0.0, kk, mask, nullptr, pa, pa);
+  hipLaunchKernelGGL(k_split_sum, dim3(nrhs), dim3(256), 0, c->stream, mask, pa, split_blocks(c), rr_dev);
+  WHMC_HIP(hipGetLastError());
+  return WHMC_OK;
+}
+
+whmc_status split_cg(whmc_ctx* c, int prec, int links, int nrhs, void* p, void* t, void* u, void* v, void* r, void* x,
+                     const double* k2, int n) {
+  SplitK2 kk{};
+  for (int q = 0; q < nrhs; ++q) kk.v[q] = k2[q];
+  auto run = [&](auto L, auto mk) {
+    const int Vh = c->Vh, nb = split_blocks(c);
+    const auto P = mk(p, Vh), T = mk(t, Vh), U = mk(u, Vh), V = mk(v, Vh);
+    using S = std::remove_cv_t<decltype(P)>;
+    constexpr bool mixed = !std::is_same<S, SpinorF64>::value;
+    std::conditional_t<mixed, SpinorF32, SpinorF64> R, X;
+    if constexpr (mixed) R = f32(r, Vh), X = f32(x, Vh);
+    else R = f64(r, Vh), X = f64(x, Vh);
+    using SR = decltype(R);
+    double* pa = c->red.partials;                 // (p, A p)
+    double* pb = pa + (size_t)kMaxRhs * nb;       // |r|^2
+    for (int it = 0; it < n; ++it) {
+      TraceRange tr(mixed ? "whmc cg iteration (mixed)" : "whmc cg iteration");
+      CGScalars* cur = c->scal;
+      CGScalars* nxt = cur == c->scal_base ? c->scal_base + kMaxRhs : c->scal_base;
+      launch_split<0, kCgHop>(c, 0, nrhs, L, P, P, T, P, R, X, 0.0, 0.0, kk, ~0u, cur, pa, pa);
+      launch_split<0, kCgU>(c, 1, nrhs, L, T, P, U, P, R, X, 0.0, 0.0, kk, ~0u, cur, pa, pa);
+      launch_split<1, kCgHop>(c, 0, nrhs, L, U, U, V, U, R, X, 0.0, 0.0, kk, ~0u, cur, pa, pa);
+      launch_split<1, kCgR>(c, 1, nrhs, L, V, U, V, P, R, X, 0.0, 0.0, kk, ~0u, cur, pa, pb);
+      hipLaunchKernelGGL((k_split_p<mixed, S, SR>), dim3(nb * nrhs), dim3(kSplitWG), 0, c->stream, fast_div(nrhs),
+                         nrhs, Vh, P, R, cur,
+                         nxt, pb, nb);
+      c->scal = nxt;
+    }
+    return WHMC_OK;
+  };
+  WHMC_TRY(with_links(c, prec, links, run));
+  WHMC_HIP(hipGetLastError());
+  return WHMC_OK;
+}
+
+}  // namespace whmc

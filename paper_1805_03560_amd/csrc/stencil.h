@@ -51,36 +51,41 @@ template <typename R> WHMC_DEV void negate(HalfSpinor<R>& h) {
     for (int c = 0; c < 3; ++c) h.c[s][c] = -h.c[s][c];
 }
 
+// the half spinor that the hop from x + DIR mu contributes to the output site, before accumulate():
+// the projected neighbour times the link (DIR = +1: U_{x,mu}, DIR = -1: U^dag_{x-mu,mu})
+template <int MU, int DIR, int DAG, class Lnk, class SIn, typename R>
+WHMC_DEV void hop_half(const Geom& g, const Coords& c, int par, int i, const Lnk& L, const SIn& in,
+                       HalfSpinor<R>& u) {
+  constexpr int SGN = (DIR > 0) == (DAG != 0) ? +1 : -1;
+  bool wrap;
+  Spinor<R> s;
+  HalfSpinor<R> h;
+  SU3<R> U;
+  const int j = neighbour<MU, DIR>(g, c, wrap);
+  in.load(j, s);
+  if (DIR > 0) L.load(par, MU, i, U);
+  else L.load(1 - par, MU, j, U);
+  project<MU, SGN>(s, h);
+  if (MU == 0 && wrap) negate(h);
+  if (DIR > 0) {
+    mul(U, h.c[0], u.c[0]);
+    mul(U, h.c[1], u.c[1]);
+  } else {
+    mul_dag(U, h.c[0], u.c[0]);
+    mul_dag(U, h.c[1], u.c[1]);
+  }
+}
+
 // contribution of direction MU (forward and backward) to the output site
 template <int MU, int DAG, class Lnk, class SIn, typename R>
 WHMC_DEV void hop_dir(const Geom& g, const Coords& c, int par, int i, const Lnk& L, const SIn& in,
                       Spinor<R>& acc) {
   constexpr int SF = DAG ? +1 : -1;  // forward hop projector sign
-  constexpr int SB = -SF;
-  bool wrap;
-  Spinor<R> s;
-  HalfSpinor<R> h, u;
-  SU3<R> U;
-  {
-    const int j = neighbour<MU, +1>(g, c, wrap);
-    in.load(j, s);
-    L.load(par, MU, i, U);
-    project<MU, SF>(s, h);
-    if (MU == 0 && wrap) negate(h);
-    mul(U, h.c[0], u.c[0]);
-    mul(U, h.c[1], u.c[1]);
-    accumulate<MU, SF>(acc, u);
-  }
-  {
-    const int j = neighbour<MU, -1>(g, c, wrap);
-    in.load(j, s);
-    L.load(1 - par, MU, j, U);
-    project<MU, SB>(s, h);
-    if (MU == 0 && wrap) negate(h);
-    mul_dag(U, h.c[0], u.c[0]);
-    mul_dag(U, h.c[1], u.c[1]);
-    accumulate<MU, SB>(acc, u);
-  }
+  HalfSpinor<R> u;
+  hop_half<MU, +1, DAG>(g, c, par, i, L, in, u);
+  accumulate<MU, SF>(acc, u);
+  hop_half<MU, -1, DAG>(g, c, par, i, L, in, u);
+  accumulate<MU, -SF>(acc, u);
 }
 
 // acc = (H psi)(x) (DAG = 0) or (H^dag psi)(x) (DAG = 1) for the site x of parity par, cb i;
