@@ -112,7 +112,7 @@ template <typename R> WHMC_DEV double norm2(const Spinor<R>& a) {
 #pragma unroll
   for (int p = 0; p < 4; ++p)
 #pragma unroll
-    for (int c = 0; c < 3; ++c) s += a.c[p][c].re * a.c[p][c].re + a.c[p][c].im * a.c[p][c].im;
+    for (int c = 0; c < 3; ++c) s = fma(a.c[p][c].im, a.c[p][c].im, fma(a.c[p][c].re, a.c[p][c].re, s));
   return double(s);
 }
 
