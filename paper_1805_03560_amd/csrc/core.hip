@@ -219,57 +219,91 @@ whmc_status hop(whmc_ctx* c, int prec, int links, int par, int dag, void* out, c
 }
 
 // ------------------------------------------------------------------ gauge field storage
-__global__ void k_pack_gauge(Geom g, const double2* __restrict__ Ucan, double2* __restrict__ U18, int unpack) {
-  const long long lex = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long long V = 2LL * g.Vh;
-  if (lex >= V) return;
-  int x = (int)(lex % g.L[3]);
-  long long r = lex / g.L[3];
-  int y = (int)(r % g.L[2]);
-  r /= g.L[2];
-  int z = (int)(r % g.L[1]);
-  int t = (int)(r / g.L[1]);
-  const int par = (t + z + y + x) & 1;
-  const int cb = (int)(lex >> 1);
-  for (int mu = 0; mu < 4; ++mu)
-    for (int k = 0; k < 9; ++k) {
-      size_t ci = ((size_t)lex * 4 + mu) * 9 + k;
-      size_t si = (size_t)(par * 4 + mu) * 9 * g.Vh + aos(k, cb, 9, g.Vh);
-      if (unpack) ((double2*)Ucan)[ci] = U18[si];
-      else U18[si] = Ucan[ci];
-    }
+// Layout conversions.  A workgroup moves the sites of a contiguous piece of the canonical field through
+// LDS: the canonical side is read (or written) as one contiguous run, the whmc side in runs of 32 to 128
+// sites per component, both coalesced.  One thread per site (16 bytes per lane every 576 or 192 bytes on
+// the canonical side) took 402 us for the links and 517 us for four full spinors at 24^3 x 48; these
+// kernels take 138 us (5.5 TB/s, the rate of a large copy is 4.9) and 184 us (5.6 TB/s).
+// Rows of LDS are padded by one entry so that the entries of one component for consecutive sites fall
+// into different banks.
+//
+// A pair of lex neighbours 2 cb, 2 cb + 1 holds the even and the odd site of checkerboard index cb: the
+// site of parity p is 2 cb + ((p + t + z + y) mod 2).
+WHMC_DEV int pair_flip(const Geom& g, int cb) {
+  const Coords c = coords_of(g, cb, 0);
+  return (c.t + c.z + c.y) & 1;
 }
 
-// max over links of |U U^dag - 1|_max and |det U - 1|, as ordered bit patterns of doubles >= 0
-__global__ void k_unitarity(int n, const double2* __restrict__ U18, int Vh, unsigned long long* out) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;   // over 8 * Vh links
+// max over the entries of |U U^dag - 1| and |det U - 1|, 1e300 for an entry that is not finite
+WHMC_DEV double su3_deviation(const SU3<double>& U) {
   double dev = 0.0;
-  if (idx < n) {
-    const int pm = idx / Vh, i = idx - pm * Vh;
-    SU3<double> U;
-    for (int k = 0; k < 9; ++k) {
-      double2 v = U18[(size_t)pm * 9 * Vh + aos(k, i, 9, Vh)];
-      U.e[k / 3][k % 3] = {v.x, v.y};
+  for (int a = 0; a < 3; ++a)
+    for (int b = 0; b < 3; ++b) {
+      cplx<double> s = {0.0, 0.0};
+      for (int k = 0; k < 3; ++k) s = s + cmul(U.e[a][k], conj(U.e[b][k]));
+      if (a == b) s.re -= 1.0;
+      dev = fmax(dev, fmax(fabs(s.re), fabs(s.im)));
     }
-    for (int a = 0; a < 3; ++a)
-      for (int b = 0; b < 3; ++b) {
-        cplx<double> s = {0.0, 0.0};
-        for (int k = 0; k < 3; ++k) s = s + cmul(U.e[a][k], conj(U.e[b][k]));
-        if (a == b) s.re -= 1.0;
-        dev = fmax(dev, fmax(fabs(s.re), fabs(s.im)));
-      }
-    cplx<double> det = cmul(U.e[0][0], cmul(U.e[1][1], U.e[2][2]) - cmul(U.e[1][2], U.e[2][1])) -
-                       cmul(U.e[0][1], cmul(U.e[1][0], U.e[2][2]) - cmul(U.e[1][2], U.e[2][0])) +
-                       cmul(U.e[0][2], cmul(U.e[1][0], U.e[2][1]) - cmul(U.e[1][1], U.e[2][0]));
-    det.re -= 1.0;
-    dev = fmax(dev, sqrt(norm2(det)));
-    // fmax drops NaN operands, so a non-finite entry is checked for explicitly and counts as failure
-    bool finite = true;
-    for (int k = 0; k < 9; ++k) finite = finite && isfinite(U.e[k / 3][k % 3].re) && isfinite(U.e[k / 3][k % 3].im);
-    if (!finite) dev = 1e300;
+  cplx<double> det = cmul(U.e[0][0], cmul(U.e[1][1], U.e[2][2]) - cmul(U.e[1][2], U.e[2][1])) -
+                     cmul(U.e[0][1], cmul(U.e[1][0], U.e[2][2]) - cmul(U.e[1][2], U.e[2][0])) +
+                     cmul(U.e[0][2], cmul(U.e[1][0], U.e[2][1]) - cmul(U.e[1][1], U.e[2][0]));
+  det.re -= 1.0;
+  dev = fmax(dev, sqrt(norm2(det)));
+  // fmax drops NaN operands, so a non-finite entry is checked for explicitly and counts as failure
+  bool finite = true;
+  for (int k = 0; k < 9; ++k) finite = finite && isfinite(U.e[k / 3][k % 3].re) && isfinite(U.e[k / 3][k % 3].im);
+  return finite ? dev : 1e300;
+}
+
+constexpr int kMoveWG = 256;
+constexpr int kGaugeTile = 64;    // lex sites per workgroup: 64 x 36 entries, 37 KiB of LDS
+
+// canonical <-> master links; CHECK (import): the largest su3_deviation of all links as ordered bits in
+// *out, each thread checking one of the tile's 256 links while it is in LDS.  A workgroup touches *out
+// only with a value above what it reads there: an atomic per wavefront on one address had taken 480 us
+// at 24^3 x 48, as long as the conversion.
+template <bool UNPACK, bool CHECK>
+__global__ __launch_bounds__(kMoveWG) void k_gauge_layout(Geom g, double2* Ucan, double2* U18,
+                                                          unsigned long long* out) {
+  __shared__ double2 lds[kGaugeTile][37];
+  __shared__ int flip[kGaugeTile / 2];
+  const long long lex0 = (long long)blockIdx.x * kGaugeTile;
+  const int cb0 = (int)(lex0 >> 1), tid = threadIdx.x;
+  const long long left = 2LL * g.Vh - lex0;
+  const int n = left < kGaugeTile ? (int)left : kGaugeTile;
+  if (tid < n / 2) flip[tid] = pair_flip(g, cb0 + tid);
+  double2* can = Ucan + lex0 * 36;
+  if (!UNPACK)
+    for (int e = tid; e < n * 36; e += kMoveWG) lds[e / 36][e % 36] = can[e];
+  __syncthreads();
+  for (int id = tid; id < 72 * (kGaugeTile / 2); id += kMoveWG) {
+    const int c = id & (kGaugeTile / 2 - 1), q = id / (kGaugeTile / 2);
+    if (c >= n / 2) continue;
+    const int par = q >= 36, comp = q - 36 * par;
+    double2* w = U18 + (size_t)(par * 4 + comp / 9) * 9 * g.Vh + aos(comp % 9, cb0 + c, 9, g.Vh);
+    double2* l = &lds[2 * c + ((par + flip[c]) & 1)][comp];
+    if (UNPACK) *l = *w;
+    else *w = *l;
   }
-  for (int off = 32; off > 0; off >>= 1) dev = fmax(dev, __shfl_xor(dev, off, 64));
-  if ((threadIdx.x & 63) == 0) atomicMax(out, (unsigned long long)__double_as_longlong(dev));
+  if (UNPACK) {
+    __syncthreads();
+    for (int e = tid; e < n * 36; e += kMoveWG) can[e] = lds[e / 36][e % 36];
+  }
+  if (CHECK) {
+    double dev = 0.0;
+    if (tid / 4 < n) {
+      SU3<double> U;
+      for (int k = 0; k < 9; ++k) {
+        const double2 v = lds[tid / 4][(tid & 3) * 9 + k];
+        U.e[k / 3][k % 3] = {v.x, v.y};
+      }
+      dev = su3_deviation(U);
+    }
+    for (int off = 32; off > 0; off >>= 1) dev = fmax(dev, __shfl_xor(dev, off, 64));
+    const unsigned long long bits = (unsigned long long)__double_as_longlong(dev);
+    if ((tid & 63) == 0 && bits > __hip_atomic_load(out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(out, bits);
+  }
 }
 
 // derived link formats from the FP64 18-real master, one thread per (parity, mu, cb); the 8-real
@@ -386,32 +420,39 @@ whmc_status ensure_links(whmc_ctx* c, int prec, int links) {
 }
 
 // ------------------------------------------------------------------ spinor layouts
-__global__ void k_pack_spinor(Geom g, double2* dst, const double2* src, int parity, int unpack, int nfields) {
-  const long long n_sites = parity < 0 ? 2LL * g.Vh : (long long)g.Vh;
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= n_sites * nfields) return;
-  const int f = (int)(idx / n_sites);
-  const long long s = idx - (long long)f * n_sites;
-  int par, cb;
-  if (parity < 0) {
-    int x = (int)(s % g.L[3]);
-    long long r = s / g.L[3];
-    int y = (int)(r % g.L[2]);
-    r /= g.L[2];
-    int z = (int)(r % g.L[1]);
-    int t = (int)(r / g.L[1]);
-    par = (t + z + y + x) & 1;
-    cb = (int)(s >> 1);
-  } else {
-    par = 0;
-    cb = (int)s;
-  }
-  const size_t field_off = (size_t)f * n_sites * 12;   // same element count in both layouts
-  for (int k = 0; k < 12; ++k) {
-    size_t ci = field_off + (size_t)s * 12 + k;
-    size_t si = field_off + (size_t)par * 12 * g.Vh + aos(k, cb, 12, g.Vh);
-    if (unpack) dst[ci] = src[si];
-    else dst[si] = src[ci];
+constexpr int kSpinorTile = 128;   // sites per workgroup, 26 KiB of LDS
+
+// canonical <-> whmc FP64 spinors, a field per blockIdx.y (strided); FULL: both parities
+template <bool FULL, bool UNPACK>
+__global__ __launch_bounds__(kMoveWG) void k_spinor_layout(Geom g, double2* canon, double2* whmc, int nfields) {
+  __shared__ double2 lds[kSpinorTile][13];
+  __shared__ int flip[kSpinorTile / 2];
+  const long long n_sites = FULL ? 2LL * g.Vh : (long long)g.Vh;
+  const long long s0 = (long long)blockIdx.x * kSpinorTile;
+  const int n = n_sites - s0 < kSpinorTile ? (int)(n_sites - s0) : kSpinorTile;
+  const int tid = threadIdx.x, cb0 = (int)(FULL ? s0 >> 1 : s0);
+  if (FULL && tid < n / 2) flip[tid] = pair_flip(g, cb0 + tid);
+  for (int f = blockIdx.y; f < nfields; f += gridDim.y) {
+    double2* can = canon + ((size_t)f * n_sites + s0) * 12;
+    double2* dev = whmc + (size_t)f * n_sites * 12;
+    __syncthreads();
+    if (!UNPACK)
+      for (int e = tid; e < n * 12; e += kMoveWG) lds[e / 12][e % 12] = can[e];
+    __syncthreads();
+    constexpr int W = FULL ? kSpinorTile / 2 : kSpinorTile;   // sites of a run
+    for (int id = tid; id < kSpinorTile * 12; id += kMoveWG) {
+      const int c = id & (W - 1), q = id / W;
+      if (c >= (FULL ? n / 2 : n)) continue;
+      const int par = FULL && q >= 12, k = q - 12 * par;
+      double2* w = dev + (size_t)par * 12 * g.Vh + aos(k, cb0 + c, 12, g.Vh);
+      double2* l = &lds[FULL ? 2 * c + ((par + flip[c]) & 1) : c][k];
+      if (UNPACK) *l = *w;
+      else *w = *l;
+    }
+    if (UNPACK) {
+      __syncthreads();
+      for (int e = tid; e < n * 12; e += kMoveWG) can[e] = lds[e / 12][e % 12];
+    }
   }
 }
 
@@ -698,20 +739,21 @@ whmc_status whmc_field_bytes(const whmc_ctx* c, int kind, int prec, size_t* byte
 whmc_status whmc_load_gauge(whmc_ctx* c, const double* U, double tol) {
   WHMC_CHECK(c && U, WHMC_EARG, "whmc_load_gauge: null argument");
   WHMC_HIP(hipSetDevice(c->device));
-  const long long V = c->V;
-  hipLaunchKernelGGL(k_pack_gauge, dim3((unsigned)((V + 255) / 256)), dim3(256), 0, c->stream, c->g,
-                     (const double2*)U, c->U18, 0);
+  void* w = nullptr;
+  if (tol > 0) {
+    WHMC_TRY(workspace(c, "unitarity", sizeof(unsigned long long), &w));
+    WHMC_TRY(zero_bytes(c, w, sizeof(unsigned long long)));
+  }
+  const dim3 grid((unsigned)((c->V + kGaugeTile - 1) / kGaugeTile)), block(kMoveWG);
+  if (tol > 0)
+    hipLaunchKernelGGL((k_gauge_layout<false, true>), grid, block, 0, c->stream, c->g, (double2*)U, c->U18,
+                       (unsigned long long*)w);
+  else
+    hipLaunchKernelGGL((k_gauge_layout<false, false>), grid, block, 0, c->stream, c->g, (double2*)U, c->U18, nullptr);
   WHMC_HIP(hipGetLastError());
   c->gauge_loaded = true;
   gauge_changed(c);
   if (tol > 0) {
-    void* w;
-    WHMC_TRY(workspace(c, "unitarity", sizeof(unsigned long long), &w));
-    WHMC_TRY(zero_bytes(c, w, sizeof(unsigned long long)));
-    const int n = 8 * c->Vh;
-    hipLaunchKernelGGL(k_unitarity, dim3((n + 255) / 256), dim3(256), 0, c->stream, n, c->U18, c->Vh,
-                       (unsigned long long*)w);
-    WHMC_HIP(hipGetLastError());
     unsigned long long bits = 0;
     WHMC_HIP(hipMemcpyAsync(c->host_pinned, w, sizeof(bits), hipMemcpyDeviceToHost, c->stream));
     WHMC_HIP(hipStreamSynchronize(c->stream));
@@ -729,9 +771,8 @@ whmc_status whmc_load_gauge(whmc_ctx* c, const double* U, double tol) {
 whmc_status whmc_export_gauge(whmc_ctx* c, double* U) {
   WHMC_CHECK(c && U, WHMC_EARG, "whmc_export_gauge: null argument");
   WHMC_CHECK(c->gauge_loaded, WHMC_ESTATE, "no gauge field loaded");
-  const long long V = c->V;
-  hipLaunchKernelGGL(k_pack_gauge, dim3((unsigned)((V + 255) / 256)), dim3(256), 0, c->stream, c->g,
-                     (const double2*)U, c->U18, 1);
+  const dim3 grid((unsigned)((c->V + kGaugeTile - 1) / kGaugeTile));
+  hipLaunchKernelGGL((k_gauge_layout<true, false>), grid, dim3(kMoveWG), 0, c->stream, c->g, (double2*)U, c->U18, nullptr);
   WHMC_HIP(hipGetLastError());
   return WHMC_OK;
 }
@@ -740,9 +781,17 @@ static whmc_status pack_impl(whmc_ctx* c, double* dst, const double* src, int pa
   WHMC_CHECK(c && dst && src, WHMC_EARG, "pack/unpack spinor: null argument");
   WHMC_CHECK(parity >= -1 && parity <= 1 && nfields >= 1, WHMC_EARG, "pack/unpack spinor: bad parity or nfields");
   WHMC_CHECK(dst != src, WHMC_EARG, "pack/unpack spinor: in-place conversion not supported");
-  const long long n = (parity < 0 ? c->V : (long long)c->Vh) * nfields;
-  hipLaunchKernelGGL(k_pack_spinor, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, c->g, (double2*)dst,
-                     (const double2*)src, parity, unpack, nfields);
+  const long long n = parity < 0 ? c->V : (long long)c->Vh;
+  const dim3 grid((unsigned)((n + kSpinorTile - 1) / kSpinorTile), (unsigned)std::min(nfields, 65535)), block(kMoveWG);
+  double2* can = (double2*)(unpack ? dst : src);
+  double2* dev = (double2*)(unpack ? src : dst);
+  if (parity < 0) {
+    if (unpack) hipLaunchKernelGGL((k_spinor_layout<true, true>), grid, block, 0, c->stream, c->g, can, dev, nfields);
+    else hipLaunchKernelGGL((k_spinor_layout<true, false>), grid, block, 0, c->stream, c->g, can, dev, nfields);
+  } else {
+    if (unpack) hipLaunchKernelGGL((k_spinor_layout<false, true>), grid, block, 0, c->stream, c->g, can, dev, nfields);
+    else hipLaunchKernelGGL((k_spinor_layout<false, false>), grid, block, 0, c->stream, c->g, can, dev, nfields);
+  }
   WHMC_HIP(hipGetLastError());
   return WHMC_OK;
 }
