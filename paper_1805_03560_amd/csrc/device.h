@@ -201,6 +201,8 @@ struct Geom {
   // XCD k owns the tx = L_t / 8 slices [k tx, (k + 1) tx) and sweeps them in chunks of tq blocks of
   // a slice, all tx slices of a chunk before the next chunk (site_block_slab); nch = ceil(nbs / tq)
   int sched, tx, tq, nch;
+  // columns of blocks (site_block_cols): blocks per z plane and z planes per XCD; zx = 0: not on this lattice
+  int nbp, zx;
 };
 
 struct Coords {
@@ -353,6 +355,25 @@ WHMC_DEV int site_block_grp(const Geom& g, int B, int nb, int G, int& grp, int& 
   const int lo = k * g.nbs / 8, hi = (k + 1) * g.nbs / 8;
   if (lo + j >= hi) return g.L[0] * g.nbs;
   return t * g.nbs + lo + j;
+}
+
+// As site_block_grp (without the slot), but where a z plane holds nbp >= 2 whole blocks and an XCD zx whole
+// planes of every slice, the XCD takes one column of nbp-th parts of its planes (L_y / nbp rows, zx
+// planes) through all time slices before the next column.  Kernels whose workgroups touch much data per
+// site and t neighbours (links of a staple, spinor pairs) then find them in L2: the workgroups in flight
+// on an XCD span several slices of a column instead of one slice, and three slices of a column fit where
+// three slices of the XCD's whole range do not; the price is the rows at the column's y edges.
+WHMC_DEV int site_block_cols(const Geom& g, int B, int nb, int G, int& grp) {
+  if (g.zx == 0) {
+    int slot;
+    return site_block_grp(g, B, nb, G, grp, slot);
+  }
+  const int k = B & 7, m = B >> 3;
+  const int j = m / G;
+  grp = m - j * G;
+  const int col = j / g.zx, z = j - col * g.zx;
+  const int yq = col / g.L[0], t = col - yq * g.L[0];
+  return t * g.nbs + (k * g.zx + z) * g.nbp + yq;
 }
 
 // Both parities in one grid of 2 nb workgroups: the XCD's m-th workgroup does parity m & 1 of its

@@ -46,6 +46,32 @@ template <typename R> WHMC_DEV void matmul_dn(const SU3<R>& A, const SU3<R>& B, 
     }
 }
 
+// C += A B, C += A B^dag, C += A^dag B
+template <typename R> WHMC_DEV void mad(const SU3<R>& A, const SU3<R>& B, SU3<R>& C) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) C.e[i][j] = cmad(A.e[i][k], B.e[k][j], C.e[i][j]);
+}
+template <typename R> WHMC_DEV void mad_nd(const SU3<R>& A, const SU3<R>& B, SU3<R>& C) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) C.e[i][j] = cjmad(B.e[j][k], A.e[i][k], C.e[i][j]);
+}
+template <typename R> WHMC_DEV void mad_dn(const SU3<R>& A, const SU3<R>& B, SU3<R>& C) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) C.e[i][j] = cjmad(A.e[k][i], B.e[k][j], C.e[i][j]);
+}
+
 WHMC_DEV void ta_coords(const SU3<double>& G, double* f) {
   const double inv_sqrt3 = 0.57735026918962576451;
   f[0] = G.e[0][1].im + G.e[1][0].im;
@@ -134,18 +160,6 @@ WHMC_DEV Site shift(const Geom& g, const Coords& c, int mu, int d, int nu = 0, i
 WHMC_DEV void load_link(const double2* U18, int Vh, Site s, int mu, SU3<double>& U) {
   LinkF64_18{U18, Vh}.load(s.par, mu, s.cb, U);
 }
-// Link-parallel grid over both parities and the 4 directions (gauge force): the 8 (parity, mu)
-// workgroups of a block of sites run back to back on one XCD (site_block_grp with 8 groups), so the
-// neighbour links they share are read from HBM once and then from its L2.  Measured at 32^3 x 64:
-// 2.8 -> 1.3 ms against parity and mu on grid.z / grid.y.
-WHMC_DEV int link_site(const Geom& g, int& par, int& mu) {
-  int grp, slot;
-  const int sb = site_block_grp(g, blockIdx.x, gridDim.x, 8, grp, slot);
-  par = grp >> 2;
-  mu = grp & 3;
-  return sb * kBlock + threadIdx.x;
-}
-
 // ------------------------------------------------------------------ plaquette
 __global__ __launch_bounds__(kBlock) void k_plaquette(Geom g, const double2* __restrict__ U18, Reduce red,
                                                       double* out) {
@@ -183,45 +197,92 @@ whmc_status plaquette_sum(whmc_ctx* c, double* host_out) {
 
 // ------------------------------------------------------------------ gauge force
 // F_{x,mu} = (beta/6) P_TA(U_{x,mu} Sigma_{x,mu}), Sigma = sum of the six staples.
-// out = (accumulate ? out : 0) + scale * F, one thread per link.
-__global__ __launch_bounds__(kBlock) void k_gauge_force(Geom g, const double2* __restrict__ U18, double* F,
-                                                        double coef, int accumulate) {
-  int par, mu;
-  const int i = link_site(g, par, mu);
+// out = (accumulate ? out : 0) + scale * F.
+//
+// A workgroup holds the four directions of 64 sites of one parity, one wavefront each; in step s the
+// wavefronts mu and nu = mu ^ s work on the plane they span, so that the links both need are read close
+// together.  Neighbours come from additive displacements of the lexicographic index and 32-bit byte
+// offsets.  It is bound by the 19 link loads per link: 24 GB through L1 and L2 per call at 32^3 x 64
+// (about 20 TB/s) with the vector units half busy and two waves per SIMD.  32^3 x 64: 1178 -> 1111 us,
+// 24^3 x 48: 375 -> 357, 12^3x24: 28.5 -> 26.1 against a workgroup per direction with 64-bit offsets.
+// Slower: sharing U_nu(x) and U_nu(x-nu) through LDS (1515 us: 74 KiB of LDS, two waves per SIMD waiting
+// at one barrier), exchanging the products U_mu(x) U_nu(x+mu) of a plane as well (1590 us: 11 loads per
+// link, six barriers), three waves per SIMD (1730 us, spills).
+WHMC_DEV void load_link_at(const double2* q, unsigned long long off, unsigned w16, SU3<double>& U) {
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const double2 v = *(const double2*)((const char*)q + (off + (unsigned long long)k * w16));
+    U.e[k / 3][k % 3] = {v.x, v.y};
+  }
+}
+WHMC_DEV void load_link_at(const double2* q, unsigned off, unsigned w16, SU3<double>& U) {
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const double2 v = *(const double2*)((const char*)q + (off + (unsigned)k * w16));
+    U.e[k / 3][k % 3] = {v.x, v.y};
+  }
+}
+// link of direction d and parity par at checkerboard index cb; Off: 32-bit byte offsets where a
+// (parity, direction) array stays below 4 GiB; FULL: no partial block
+template <bool FULL, class Off>
+WHMC_DEV void link_at(const double2* U18, int Vh, int par, int d, int cb, SU3<double>& U) {
+  const int blk = cb >> 6;
+  const unsigned w16 = (FULL || blk < (Vh >> 6) ? 64u : (unsigned)(Vh & 63)) * 16u;
+  load_link_at(U18 + (size_t)(par * 4 + d) * 9 * Vh, (Off)blk * (64u * 9u * 16u) + (Off)(cb & 63) * 16u,
+               FULL ? 1024u : w16, U);
+}
+
+constexpr int kStapleWG = 256;
+
+template <bool FULL, class Off>
+__global__ __launch_bounds__(kStapleWG, 2) void k_gauge_force(Geom g, const double2* __restrict__ U18, double* F,
+                                                           double coef, int accumulate) {
+  int grp;
+  const int sb = site_block_cols(g, blockIdx.x, gridDim.x, 4, grp);
+  const int base = sb * kBlock + (grp & 1) * 64, par = grp >> 1;
+  const int lane = threadIdx.x & 63, mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i = base + lane;
   if (i >= g.Vh) return;
   const Coords c = coords_of(g, i, par);
-  SU3<double> S, a, b, d, t1, t2;
+  const int lex = 2 * i + (c.x & 1);
+  // displacements of the lexicographic index by one step (with wrap): steps of different directions add up
+  const int s2 = g.L[3], s1 = s2 * g.L[2], s0 = s1 * g.L[1];
+  const int f0 = c.t + 1 == g.L[0] ? s0 - s0 * g.L[0] : s0, b0 = c.t == 0 ? s0 * g.L[0] - s0 : -s0;
+  const int f1 = c.z + 1 == g.L[1] ? s1 - s1 * g.L[1] : s1, b1 = c.z == 0 ? s1 * g.L[1] - s1 : -s1;
+  const int f2 = c.y + 1 == g.L[2] ? s2 - s2 * g.L[2] : s2, b2 = c.y == 0 ? s2 * g.L[2] - s2 : -s2;
+  const int f3 = c.x + 1 == g.L[3] ? 1 - g.L[3] : 1, b3 = c.x == 0 ? g.L[3] - 1 : -1;
+  const int fm = mu == 0 ? f0 : mu == 1 ? f1 : mu == 2 ? f2 : f3;
+  SU3<double> S;
+#pragma unroll
   for (int p = 0; p < 3; ++p)
+#pragma unroll
     for (int q = 0; q < 3; ++q) S.e[p][q] = {0.0, 0.0};
-  for (int nu = 0; nu < 4; ++nu) {
-    if (nu == mu) continue;
+#pragma unroll 1
+  for (int s = 1; s < 4; ++s) {
+    const int nu = mu ^ s;
+    const int fn = nu == 0 ? f0 : nu == 1 ? f1 : nu == 2 ? f2 : f3;
+    const int bn = nu == 0 ? b0 : nu == 1 ? b1 : nu == 2 ? b2 : b3;
+    SU3<double> a, b, T;
     // up: U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
-    load_link(U18, g.Vh, shift(g, c, mu, 1), nu, a);
-    load_link(U18, g.Vh, shift(g, c, nu, 1), mu, b);
-    load_link(U18, g.Vh, Site{par, i}, nu, d);
-    matmul_nd(a, b, t1);
-    matmul_nd(t1, d, t2);
-    for (int p = 0; p < 3; ++p)
-      for (int q = 0; q < 3; ++q) S.e[p][q] = S.e[p][q] + t2.e[p][q];
-    // down: U_nu(x+mu-nu)^dag U_mu(x-nu)^dag U_nu(x-nu)
-    load_link(U18, g.Vh, shift(g, c, mu, 1, nu, -1), nu, a);
-    load_link(U18, g.Vh, shift(g, c, nu, -1), mu, b);
-    load_link(U18, g.Vh, shift(g, c, nu, -1), nu, d);
-    {
-      SU3<double> ad;   // a^dag, then t1 = a^dag b^dag
-      for (int p = 0; p < 3; ++p)
-        for (int q = 0; q < 3; ++q) ad.e[p][q] = conj(a.e[q][p]);
-      matmul_nd(ad, b, t1);
-    }
-    matmul(t1, d, t2);
-    for (int p = 0; p < 3; ++p)
-      for (int q = 0; q < 3; ++q) S.e[p][q] = S.e[p][q] + t2.e[p][q];
+    link_at<FULL, Off>(U18, g.Vh, 1 - par, nu, (lex + fm) >> 1, a);
+    link_at<FULL, Off>(U18, g.Vh, 1 - par, mu, (lex + fn) >> 1, b);
+    matmul_nd(a, b, T);
+    link_at<FULL, Off>(U18, g.Vh, par, nu, i, a);
+    mad_nd(T, a, S);
+    // down: (U_mu(x-nu) U_nu(x+mu-nu))^dag U_nu(x-nu)
+    link_at<FULL, Off>(U18, g.Vh, 1 - par, mu, (lex + bn) >> 1, a);
+    link_at<FULL, Off>(U18, g.Vh, par, nu, (lex + fm + bn) >> 1, b);
+    matmul(a, b, T);
+    link_at<FULL, Off>(U18, g.Vh, 1 - par, nu, (lex + bn) >> 1, a);
+    mad_dn(T, a, S);
   }
-  load_link(U18, g.Vh, Site{par, i}, mu, a);
-  matmul(a, S, t1);
+  SU3<double> U, G;
+  link_at<FULL, Off>(U18, g.Vh, par, mu, i, U);
+  matmul(U, S, G);
   double f[8];
-  ta_coords(t1, f);
+  ta_coords(G, f);
   double* out = F + ((size_t)(par * 4 + mu) * 8) * g.Vh + i;
+#pragma unroll
   for (int k = 0; k < 8; ++k) {
     const double v = coef * f[k];
     out[(size_t)k * g.Vh] = accumulate ? out[(size_t)k * g.Vh] + v : v;
@@ -230,9 +291,16 @@ __global__ __launch_bounds__(kBlock) void k_gauge_force(Geom g, const double2* _
 
 whmc_status gauge_force(whmc_ctx* c, double* F, double beta_eff, double scale, int accumulate) {
   WHMC_CHECK(c->gauge_loaded, WHMC_ESTATE, "no gauge field loaded");
-  const dim3 grid(8 * c->stencil_blocks());
-  hipLaunchKernelGGL(k_gauge_force, grid, dim3(kBlock), 0, c->stream, c->g, c->U18, F, scale * beta_eff / 6.0,
-                     accumulate);
+  const dim3 grid(4 * c->stencil_blocks()), block(kStapleWG);
+  const double coef = scale * beta_eff / 6.0;
+  const bool narrow = (unsigned long long)c->Vh * 144ull <= 0xFFFFFFFFull;
+  if (!narrow)
+    hipLaunchKernelGGL((k_gauge_force<false, unsigned long long>), grid, block, 0, c->stream, c->g, c->U18, F, coef,
+                       accumulate);
+  else if (c->Vh % 64 == 0)
+    hipLaunchKernelGGL((k_gauge_force<true, unsigned>), grid, block, 0, c->stream, c->g, c->U18, F, coef, accumulate);
+  else
+    hipLaunchKernelGGL((k_gauge_force<false, unsigned>), grid, block, 0, c->stream, c->g, c->U18, F, coef, accumulate);
   WHMC_HIP(hipGetLastError());
   return WHMC_OK;
 }
@@ -402,8 +470,8 @@ constexpr int kForceWG = 512;
 
 __global__ __launch_bounds__(kForceWG) void k_pf_force(Geom g, const double2* __restrict__ U18, PairPtrs P,
                                                        int npairs, double kappa_eff, double* F, int accumulate) {
-  int half, slot;
-  const int sb = site_block_grp(g, blockIdx.x, gridDim.x, 2, half, slot);
+  int half;
+  const int sb = site_block_cols(g, blockIdx.x, gridDim.x, 2, half);
   const int base = sb * kBlock + half * 64;
   if (base >= g.Vh) return;   // the whole workgroup: no barrier is left waiting
   const int par = threadIdx.x >> 8, mu = (threadIdx.x >> 6) & 3;
