@@ -212,7 +212,7 @@ whmc_status hop_full(whmc_ctx* c, int prec, int links, int dag, void* out, const
 whmc_status hop(whmc_ctx* c, int prec, int links, int par, int dag, void* out, const void* in, const void* x,
                 double a, double b, double* norm_out, bool nt_store) {
   WHMC_TRY(ensure_links(c, prec, links));
-  if (!norm_out && split_hops(c, prec, links, 1)) return split_hop(c, prec, links, par, dag, 1, out, in, x, a, b);
+  if (!norm_out && split_hops(c, prec, links, 1)) return split_hop(c, prec, links, par, dag, 1, out, in, x, a, &b);
   const bool nt = c->stream_links(prec, links);
   if (nt) return hop_nt<true>(c, prec, links, par, dag, out, in, x, a, b, norm_out, nt_store && nt);
   return hop_nt<false>(c, prec, links, par, dag, out, in, x, a, b, norm_out, false);
@@ -830,25 +830,66 @@ whmc_status whmc_apply_Moo(whmc_ctx* c, double* out, const double* in, double ka
   return apply_Moo_f64(c, out, in, kappa, dagger ? 1 : 0, (double*)tmp);
 }
 
+// How many of nrhs right-hand sides one pass of M^dag M takes: as many as the direction-split kernels of
+// small lattices allow; on larger lattices the even/odd operator takes up to four through the multi-RHS
+// kernels (57 to 79 us per rhs and hop at 24^3 x 48 against 98, most of it gained by the second; the
+// batch's scratch grows with it) and the full one, whose kernels have no multi-RHS form, one.
+static int mdagm_batch(const whmc_ctx* c, int nrhs, int eo) {
+  for (int n = std::min(nrhs, kMaxRhs); n >= 1; --n)
+    if (split_hops(c, WHMC_F64, WHMC_L18, eo ? n : 2 * n)) return n;
+  return eo && !c->split_off ? std::min(nrhs, 4) : 1;
+}
+
+// out_r = A(kappa_r) in_r for a batch that mdagm_batch chose; w: n * V * 192 bytes
+static whmc_status mdagm_some(whmc_ctx* c, double* out, const double* in, const double* kappas, int n, int eo, double* w) {
+  const size_t h = (size_t)24 * c->Vh;
+  if (!eo) {
+    if (!split_hops(c, WHMC_F64, WHMC_L18, 2 * n)) return apply_MdagM_full(c, out, in, kappas[0], w);
+    WHMC_TRY(split_fullM(c, 0, n, w, in, kappas));
+    return split_fullM(c, 1, n, out, w, kappas);
+  }
+  double* te = w;
+  double* to = w + n * h;
+  if (split_hops(c, WHMC_F64, WHMC_L18, n)) {
+    double one[kMaxRhs], b[kMaxRhs];
+    for (int r = 0; r < n; ++r) one[r] = 1.0, b[r] = -kappas[r] * kappas[r];
+    WHMC_TRY(split_hop(c, WHMC_F64, WHMC_L18, 0, 0, n, te, in, nullptr, 0.0, one));
+    WHMC_TRY(split_hop(c, WHMC_F64, WHMC_L18, 1, 0, n, to, te, in, 1.0, b));
+    WHMC_TRY(split_hop(c, WHMC_F64, WHMC_L18, 0, 1, n, te, to, nullptr, 0.0, one));
+    return split_hop(c, WHMC_F64, WHMC_L18, 1, 1, n, out, te, to, 1.0, b);
+  }
+  if (n > 1) return apply_MdagM_multi(c, out, in, kappas, n, te, to);
+  return apply_MdagM_f64(c, out, in, kappas[0], te, to);
+}
+
 whmc_status whmc_apply_MdagM(whmc_ctx* c, double* out, const double* in, const double* kappas, int nrhs, int eo) {
   WHMC_CHECK(c && out && in && kappas && nrhs >= 1, WHMC_EARG, "whmc_apply_MdagM: bad argument");
   WHMC_CHECK(out != in, WHMC_EARG, "whmc_apply_MdagM: in and out must differ");
   WHMC_CHECK(eo == 0 || eo == 1, WHMC_EARG, "whmc_apply_MdagM: eo must be 0 (full lattice) or 1 (even/odd)");
   WHMC_CHECK(c->gauge_loaded, WHMC_ESTATE, "no gauge field loaded");
-  const size_t hb = (size_t)c->Vh * 192;
-  if (!eo) {
-    void* tf;
-    WHMC_TRY(workspace(c, "mdm_tmp_full", 2 * hb, &tf));
-    for (int r = 0; r < nrhs; ++r)
-      WHMC_TRY(apply_MdagM_full(c, out + (size_t)r * 48 * c->Vh, in + (size_t)r * 48 * c->Vh, kappas[r], (double*)tf));
-    return WHMC_OK;
+  // a batch's intermediates: an even and an odd half field (eo = 1) or a full field (eo = 0) per rhs
+  int done = 0;
+  while (done < nrhs) {
+    const size_t f = (size_t)(eo ? 24 : 48) * c->Vh;
+    const size_t per = (size_t)c->Vh * 384;
+    int n = mdagm_batch(c, nrhs - done, eo);
+    // a larger scratch than there is cannot be had while the stream is captured: take smaller batches then
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const auto have = c->ws.find("mdm_tmp");
+    if (have != c->ws.end() && have->second.second < n * per &&
+        hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone)
+      n = std::max(1, (int)(have->second.second / per));
+    void* w = nullptr;
+    whmc_status rc = workspace(c, "mdm_tmp", n * per, &w);
+    if (rc == WHMC_EHIP && n > 1) {   // no memory for the batch
+      (void)hipGetLastError();
+      n = 1;
+      rc = workspace(c, "mdm_tmp", per, &w);
+    }
+    WHMC_TRY(rc);
+    WHMC_TRY(mdagm_some(c, out + done * f, in + done * f, kappas + done, n, eo, (double*)w));
+    done += n;
   }
-  void *te, *to;
-  WHMC_TRY(workspace(c, "mdm_tmp_even", hb, &te));
-  WHMC_TRY(workspace(c, "mdm_tmp_odd", hb, &to));
-  for (int r = 0; r < nrhs; ++r)
-    WHMC_TRY(apply_MdagM_f64(c, out + (size_t)r * 24 * c->Vh, in + (size_t)r * 24 * c->Vh, kappas[r], (double*)te,
-                             (double*)to));
   return WHMC_OK;
 }
 
@@ -865,13 +906,13 @@ whmc_status whmc_apply_MdagM_noalloc(whmc_ctx* c, double* out, const double* in,
              "whmc_apply_MdagM_noalloc: the lattice needs " + std::to_string(2 * hb) + " bytes of scratch, more than the " +
                  std::to_string(kNoAllocScratch) + " bytes of the static buffer (V <= " +
                  std::to_string(kNoAllocScratch / 192) + " sites)");
-  double* t0 = (double*)c->noalloc_scratch;
-  double* t1 = (double*)((char*)c->noalloc_scratch + hb);
-  for (int r = 0; r < nrhs; ++r) {
-    if (eo)
-      WHMC_TRY(apply_MdagM_f64(c, out + (size_t)r * 24 * c->Vh, in + (size_t)r * 24 * c->Vh, kappas[r], t0, t1));
-    else
-      WHMC_TRY(apply_MdagM_full(c, out + (size_t)r * 48 * c->Vh, in + (size_t)r * 48 * c->Vh, kappas[r], t0));
+  const int room = (int)std::min<size_t>(kNoAllocScratch / (2 * hb), (size_t)nrhs);
+  int done = 0;
+  while (done < nrhs) {
+    const size_t f = (size_t)(eo ? 24 : 48) * c->Vh;
+    const int n = mdagm_batch(c, std::min(nrhs - done, room), eo);
+    WHMC_TRY(mdagm_some(c, out + done * f, in + done * f, kappas + done, n, eo, (double*)c->noalloc_scratch));
+    done += n;
   }
   return WHMC_OK;
 }

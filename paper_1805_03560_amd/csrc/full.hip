@@ -139,6 +139,7 @@ static void launch_fullM(whmc_ctx* c, const Lnk& L, int dagger, double* out, con
 
 whmc_status apply_M_full(whmc_ctx* c, double* out, const double* in, double kappa, int dagger) {
   WHMC_CHECK(c->gauge_loaded, WHMC_ESTATE, "no gauge field loaded");
+  if (split_hops(c, WHMC_F64, WHMC_L18, 2)) return split_fullM(c, dagger, 1, out, in, &kappa);
   if (c->stream_links(WHMC_F64, WHMC_L18)) launch_fullM(c, LinkF64_18T<true>{c->U18, c->Vh}, dagger, out, in, kappa);
   else launch_fullM(c, LinkF64_18T<false>{c->U18, c->Vh}, dagger, out, in, kappa);
   WHMC_HIP(hipGetLastError());

@@ -174,7 +174,9 @@ whmc_status hop(whmc_ctx* c, int prec, int links, int par, int dag, void* out, c
 // ---- direction-split kernels for small lattices (split.hip)
 bool split_hops(const whmc_ctx* c, int prec, int links, int nrhs);   // whether this call takes them
 whmc_status split_hop(whmc_ctx* c, int prec, int links, int par, int dag, int nrhs, void* out, const void* in,
-                      const void* x, double a, double b);
+                      const void* x, double a, const double* b);   // b[nrhs]
+// out_r = M(kappa_r)^(dag) in_r on nrhs <= kMaxRhs full spinors, FP64 with 18-real links
+whmc_status split_fullM(whmc_ctx* c, int dag, int nrhs, double* out, const double* in, const double* kappas);
 // rr_dev[q] = |r_q|^2, r_q = b_q - A(kappa_q) x_q for the right-hand sides q in mask, FP64 with 18-real links
 whmc_status split_residual(whmc_ctx* c, unsigned mask, int nrhs, const double* x, const double* b, const double* k2,
                            void* t, void* u, void* v, void* r, double* rr_dev);
@@ -203,6 +205,10 @@ whmc_status apply_K_f64(whmc_ctx* c, double* out, const double* in, double kappa
 // full lattice (full spinors = even half, odd half): out = M in or M^dag in, M = 1 - kappa H (full.hip)
 whmc_status apply_M_full(whmc_ctx* c, double* out, const double* in, double kappa, int dagger);
 whmc_status apply_MdagM_full(whmc_ctx* c, double* out, const double* in, double kappa, double* tmp_full);
+
+// out_r = A(kappa_r) in_r, A = M_oo^dag M_oo, through the multi-RHS kernels (multi.hip); te, to: nrhs half fields each
+whmc_status apply_MdagM_multi(whmc_ctx* c, double* out, const double* in, const double* kappas, int nrhs, double* te,
+                              double* to);
 
 // ---- solvers (cg.hip)
 whmc_status cg_solve(whmc_ctx* c, double* x, const double* b, const double* kappas, int nrhs,

@@ -224,8 +224,8 @@ __global__ __launch_bounds__(kBlock) void k_mcg3(Geom g, int G, int order, Lnk L
   mhop_body<1>(g, 0, m, L, u0, v0, live);
 }
 
-// CG kernel 2: u = p - kappa^2 H_oe t, |u|^2 = (p, A p)
-template <int NB, int R, class Lnk, class S, class P>
+// CG kernel 2: u = p - kappa^2 H_oe^(DAG) t, |u|^2 = (p, A p)
+template <int DAG, int NB, int R, class Lnk, class S, class P>
 __global__ __launch_bounds__(kBlock) void k_mcg2(Geom g, int nrhs, int G, int order, Lnk L, S t0, S p0, S u0, K2 k2, P live,
                                                  Reduce red, int nslots) {
   using Re = typename S::Real;
@@ -245,7 +245,7 @@ __global__ __launch_bounds__(kBlock) void k_mcg2(Geom g, int nrhs, int G, int or
     }
     if (any) {
       Spinor<Re> acc[NB];
-      hop_site_multi<0, NB>(g, 1, m.i, L, in, act, acc);
+      hop_site_multi<DAG, NB>(g, 1, m.i, L, in, act, acc);
 #pragma unroll
       for (int k = 0; k < NB; ++k) {
         if (!act[k]) continue;
@@ -714,7 +714,7 @@ static void enqueue_multi(whmc_ctx* c, int nrhs, int order, const Lnk& L, S p, S
   for (int it = 0; it < n; ++it) {
     TraceRange tr("whmc multi-rhs cg iteration");
     hipLaunchKernelGGL((k_mcg1<NB, R, Lnk, S, ByScalars>), grid, block, 0, c->stream, c->g, G, order, L, p, t, live);
-    hipLaunchKernelGGL((k_mcg2<NB, R, Lnk, S, ByScalars>), grid, block, 0, c->stream, c->g, nrhs, G, order, L, t, p, u,
+    hipLaunchKernelGGL((k_mcg2<0, NB, R, Lnk, S, ByScalars>), grid, block, 0, c->stream, c->g, nrhs, G, order, L, t, p, u,
                        k2,
                        live, c->red, ns);
     hipLaunchKernelGGL(k_mcg2_fin, dim3(nrhs), dim3(256), 0, c->stream, c->scal, nrhs, c->red.partials, ns * R);
@@ -738,7 +738,7 @@ static void enqueue_residual(whmc_ctx* c, unsigned mask, int nrhs, int order, co
   const dim3 grid(ns * G * R), block(kBlock);
   const BySet live{mask, nrhs};
   hipLaunchKernelGGL((k_mcg1<1, R, Lnk, SpinorF64, BySet>), grid, block, 0, c->stream, c->g, G, order, L, x, t, live);
-  hipLaunchKernelGGL((k_mcg2<1, R, Lnk, SpinorF64, BySet>), grid, block, 0, c->stream, c->g, nrhs, G, order, L, t, x,
+  hipLaunchKernelGGL((k_mcg2<0, 1, R, Lnk, SpinorF64, BySet>), grid, block, 0, c->stream, c->g, nrhs, G, order, L, t, x,
                      u, k2,
                      live, c->red, ns);
   hipLaunchKernelGGL((k_mcg3<1, R, Lnk, SpinorF64, BySet>), grid, block, 0, c->stream, c->g, G, order, L, u, v, live);
@@ -766,6 +766,38 @@ static whmc_status residual_multi(whmc_ctx* c, unsigned mask, int nrhs, const do
   const Blocking b1{1, bk.lanes, bk.order};   // the residual kernels hold one rhs per thread
   if (stream_multi(c, WHMC_F64, WHMC_L18, nrhs, b1)) WHMC_TRY(run(LinkF64_18T<true>{c->U18, Vh}));
   else WHMC_TRY(run(LinkF64_18T<false>{c->U18, Vh}));
+  WHMC_HIP(hipGetLastError());
+  return WHMC_OK;
+}
+
+// M_oo^dag M_oo on nrhs >= 2 right-hand sides with two lanes per site (the blocking that wins in FP64 at
+// every size where the single-rhs chain is the alternative): a link is read once for two of them.
+// 24^3 x 48, two rhs: XX
+template <class Lnk>
+static void enqueue_mdagm(whmc_ctx* c, int nrhs, const Lnk& L, SpinorF64 x, SpinorF64 out, const K2& k2, SpinorF64 te,
+                          SpinorF64 to) {
+  constexpr int R = 2;
+  const int G = (nrhs + R - 1) / R, ns = c->stencil_blocks();
+  const dim3 grid(ns * G * R), block(kBlock);
+  const BySet live{~0u, nrhs};
+  hipLaunchKernelGGL((k_mcg1<1, R, Lnk, SpinorF64, BySet>), grid, block, 0, c->stream, c->g, G, 0, L, x, te, live);
+  hipLaunchKernelGGL((k_mcg2<0, 1, R, Lnk, SpinorF64, BySet>), grid, block, 0, c->stream, c->g, nrhs, G, 0, L, te, x, to,
+                     k2, live, c->red, ns);
+  hipLaunchKernelGGL((k_mcg3<1, R, Lnk, SpinorF64, BySet>), grid, block, 0, c->stream, c->g, G, 0, L, to, te, live);
+  hipLaunchKernelGGL((k_mcg2<1, 1, R, Lnk, SpinorF64, BySet>), grid, block, 0, c->stream, c->g, nrhs, G, 0, L, te, to,
+                     out, k2, live, c->red, ns);
+}
+
+whmc_status apply_MdagM_multi(whmc_ctx* c, double* out, const double* in, const double* kappas, int nrhs, double* te,
+                              double* to) {
+  K2 k2{};
+  for (int r = 0; r < nrhs; ++r) k2.v[r] = kappas[r] * kappas[r];
+  const int Vh = c->Vh;
+  if (stream_multi(c, WHMC_F64, WHMC_L18, nrhs, Blocking{1, 2, 0}))
+    enqueue_mdagm(c, nrhs, LinkF64_18T<true>{c->U18, Vh}, h64((void*)in, Vh), h64(out, Vh), k2, h64(te, Vh), h64(to, Vh));
+  else
+    enqueue_mdagm(c, nrhs, LinkF64_18T<false>{c->U18, Vh}, h64((void*)in, Vh), h64(out, Vh), k2, h64(te, Vh),
+                  h64(to, Vh));
   WHMC_HIP(hipGetLastError());
   return WHMC_OK;
 }
@@ -980,8 +1012,11 @@ extern "C" whmc_status whmc_apply_H_multi(whmc_ctx* c, void* out, const void* in
   WHMC_CHECK(c && out && in && out != in, WHMC_EARG, "whmc_apply_H_multi: bad pointers");
   WHMC_CHECK(out_parity == 0 || out_parity == 1, WHMC_EARG, "whmc_apply_H_multi: out_parity must be 0 or 1");
   WHMC_CHECK(nrhs >= 1 && nrhs <= kMaxRhs, WHMC_EARG, "whmc_apply_H_multi: nrhs must be in [1, 16]");
-  if (rhs_block <= 0 && rhs_lanes <= 0 && split_format(prec, links) && split_hops(c, prec, links, nrhs))
-    return split_hop(c, prec, links, out_parity, dagger ? 1 : 0, nrhs, out, in, nullptr, 0.0, 1.0);
+  if (rhs_block <= 0 && rhs_lanes <= 0 && split_format(prec, links) && split_hops(c, prec, links, nrhs)) {
+    double ones[kMaxRhs];
+    for (double& v : ones) v = 1.0;
+    return split_hop(c, prec, links, out_parity, dagger ? 1 : 0, nrhs, out, in, nullptr, 0.0, ones);
+  }
   Blocking b;
   WHMC_TRY(resolve_blocking(c, prec, links, nrhs, rhs_block, rhs_lanes, rhs_order, &b));
   return mhop(c, prec, links, out_parity, dagger ? 1 : 0, nrhs, b, out, in);

@@ -125,9 +125,10 @@ WHMC_DEV void pin(const Geom& g, const void* links, const void* in) {
 }
 
 // ------------------------------------------------------------------ kernels
-enum { kPlain, kXpay, kCgHop, kCgU, kCgR, kRes };
+enum { kPlain, kXpay, kFullM, kCgHop, kCgU, kCgR, kRes };
 
-// MODE kPlain: out = b H in;  kXpay: out = a x + b H in;  and the steps of a CG iteration, which skip a
+// MODE kPlain: out = k2 H in;  kXpay: out = a x + k2 H in;  kFullM: out = x - k2 H in on the whole lattice,
+// where field 2 r + parity is a half of full field r;  and the steps of a CG iteration, which skip a
 // stopped right-hand side:  kCgHop: out = H in;  kCgU: out = x - k2 H in, |out|^2 to part_out;
 // kCgR: with (p, A p) from part_in, alpha = |r|^2 / (p, A p), A p = x - k2 H in, r -= alpha A p,
 // xs += alpha p, |r|^2 to part_out.  kRes: out = p - (x - k2 H in), |out|^2 to part_out (the last hop of a
@@ -135,7 +136,7 @@ enum { kPlain, kXpay, kCgHop, kCgU, kCgR, kRes };
 // (sc may be null: none is).
 template <int DAG, int MODE, class Lnk, class S, class SR>
 __global__ __launch_bounds__(kSplitWG) void k_split(FastDiv by_nrhs, int nrhs, unsigned mask, CGScalars* sc, Geom g, int par,
-                                                    Lnk L, S in0, S x0, S out0, S p0, SR r0, SR xs0, double a, double b,
+                                                    Lnk L, S in0, S x0, S out0, S p0, SR r0, SR xs0, double a,
                                                     const double* part_in, double* part_out, int nb, SplitK2 k2) {
   using R = typename S::Real;
   using RR = typename SR::Real;
@@ -144,7 +145,8 @@ __global__ __launch_bounds__(kSplitWG) void k_split(FastDiv by_nrhs, int nrhs, u
   const int sb = by_nrhs.div(B), r = B - sb * nrhs;
   pin(g, L.p, in0.p);
   // scalars of the epilogue, read now so that their latency overlaps the hop
-  const R kk = MODE == kCgU || MODE == kCgR || MODE == kRes ? R(k2.v[r]) : R(0);
+  const R kk = MODE == kCgHop ? R(0) : R(k2.v[MODE == kFullM ? r >> 1 : r]);
+  if (MODE == kFullM) par = r & 1;
   const double rr_cur = MODE == kCgR ? sc[r].rr : 0.0;
   if (cg && (!((mask >> r) & 1u) || (sc && (sc[r].done | sc[r].pause)))) return;
   __shared__ cplx<R> lds[8][6][kSplitRow];
@@ -160,7 +162,7 @@ __global__ __launch_bounds__(kSplitWG) void k_split(FastDiv by_nrhs, int nrhs, u
   cplx<RR> rv[2], xsv[2];
   if (i < g.Vh) {
     const Coords c = coords_of(g, i, par);
-    const S in = field(in0, r);
+    const S in = field(in0, MODE == kFullM ? r ^ 1 : r);
     HalfSpinor<R> u;
     switch (wave) {
       case 0: hop_half<0, +1, DAG>(g, c, par, i, L, in, u); break;
@@ -215,9 +217,9 @@ __global__ __launch_bounds__(kSplitWG) void k_split(FastDiv by_nrhs, int nrhs, u
     if (act) {
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        if (MODE == kPlain) acc[j] = R(b) * acc[j];
-        if (MODE == kXpay) acc[j] = R(a) * xv[j] + R(b) * acc[j];
-        if (MODE == kCgU) acc[j] = xv[j] - kk * acc[j];
+        if (MODE == kPlain) acc[j] = kk * acc[j];
+        if (MODE == kXpay) acc[j] = R(a) * xv[j] + kk * acc[j];
+        if (MODE == kCgU || MODE == kFullM) acc[j] = xv[j] - kk * acc[j];
         if (MODE == kRes) acc[j] = pv[j] - (xv[j] - kk * acc[j]);
       }
       if (MODE == kCgU || MODE == kRes) nrm = double(norm2(acc[0]) + norm2(acc[1]));
@@ -333,20 +335,22 @@ bool split_hops(const whmc_ctx* c, int prec, int links, int nrhs) {
 
 template <int DAG, int MODE, class Lnk, class S, class SR>
 static void launch_split(whmc_ctx* c, int par, int nrhs, const Lnk& L, S in, S x, S out, S p, SR r, SR xs, double a,
-                         double b, const SplitK2& k2, unsigned mask, CGScalars* sc, const double* part_in,
+                         const SplitK2& k2, unsigned mask, CGScalars* sc, const double* part_in,
                          double* part_out) {
   const int nb = split_blocks(c);
   hipLaunchKernelGGL((k_split<DAG, MODE, Lnk, S, SR>), dim3(nb * nrhs), dim3(kSplitWG), 0, c->stream, fast_div(nrhs),
-                     nrhs, mask, sc, c->g, par, L, in, x, out, p, r, xs, a, b, part_in, part_out, nb, k2);
+                     nrhs, mask, sc, c->g, par, L, in, x, out, p, r, xs, a, part_in, part_out, nb, k2);
 }
 
 whmc_status split_hop(whmc_ctx* c, int prec, int links, int par, int dag, int nrhs, void* out, const void* in,
-                      const void* x, double a, double b) {
+                      const void* x, double a, const double* b) {
+  SplitK2 kb{};
+  for (int q = 0; q < nrhs; ++q) kb.v[q] = b[q];
   auto run = [&](auto L, auto mk) {
     const auto I = mk(in, c->Vh), X = mk(x, c->Vh), O = mk(out, c->Vh);
     auto go = [&](auto dagc, auto mode) {
-      launch_split<decltype(dagc)::value, decltype(mode)::value>(c, par, nrhs, L, I, X, O, X, X, X, a, b, SplitK2{}, 0u,
-                                                                 nullptr, nullptr, nullptr);
+      launch_split<decltype(dagc)::value, decltype(mode)::value>(c, par, nrhs, L, I, X, O, X, X, X, a, kb, 0u, nullptr,
+                                                                 nullptr, nullptr);
     };
     using D0 = std::integral_constant<int, 0>;
     using D1 = std::integral_constant<int, 1>;
@@ -357,6 +361,17 @@ whmc_status split_hop(whmc_ctx* c, int prec, int links, int par, int dag, int nr
     return WHMC_OK;
   };
   WHMC_TRY(with_links(c, prec, links, run));
+  WHMC_HIP(hipGetLastError());
+  return WHMC_OK;
+}
+
+whmc_status split_fullM(whmc_ctx* c, int dag, int nrhs, double* out, const double* in, const double* kappas) {
+  SplitK2 kk{};
+  for (int q = 0; q < nrhs; ++q) kk.v[q] = kappas[q];
+  const LinkF64_18T<false> L{c->U18, c->Vh};
+  const SpinorF64 I = f64(in, c->Vh), O = f64(out, c->Vh);
+  if (dag) launch_split<1, kFullM>(c, 0, 2 * nrhs, L, I, I, O, I, I, I, 0.0, kk, 0u, nullptr, nullptr, nullptr);
+  else launch_split<0, kFullM>(c, 0, 2 * nrhs, L, I, I, O, I, I, I, 0.0, kk, 0u, nullptr, nullptr, nullptr);
   WHMC_HIP(hipGetLastError());
   return WHMC_OK;
 }
@@ -377,10 +392,10 @@ whmc_status split_residual(whmc_ctx* c, unsigned mask, int nrhs, const double* x
   const LinkF64_18T<false> L{c->U18, Vh};
   const SpinorF64 X = f64(x, Vh), B = f64(b, Vh), T = f64(t, Vh), U = f64(u, Vh), V = f64(v, Vh), R = f64(r, Vh);
   double* pa = c->red.partials;
-  launch_split<0, kCgHop>(c, 0, nrhs, L, X, X, T, X, R, R, 0.0, 0.0, kk, mask, nullptr, pa, pa);
-  launch_split<0, kCgU>(c, 1, nrhs, L, T, X, U, X, R, R, 0.0, 0.0, kk, mask, nullptr, pa, pa);
-  launch_split<1, kCgHop>(c, 0, nrhs, L, U, U, V, U, R, R, 0.0, 0.0, kk, mask, nullptr, pa, pa);
-  launch_split<1, kRes>(c, 1, nrhs, L, V, U, R, B, R, R, 0.0, 0.0, kk, mask, nullptr, pa, pa);
+  launch_split<0, kCgHop>(c, 0, nrhs, L, X, X, T, X, R, R, 0.0, kk, mask, nullptr, pa, pa);
+  launch_split<0, kCgU>(c, 1, nrhs, L, T, X, U, X, R, R, 0.0, kk, mask, nullptr, pa, pa);
+  launch_split<1, kCgHop>(c, 0, nrhs, L, U, U, V, U, R, R, 0.0, kk, mask, nullptr, pa, pa);
+  launch_split<1, kRes>(c, 1, nrhs, L, V, U, R, B, R, R, 0.0, kk, mask, nullptr, pa, pa);
   hipLaunchKernelGGL(k_split_sum, dim3(nrhs), dim3(256), 0, c->stream, mask, pa, split_blocks(c), rr_dev);
   WHMC_HIP(hipGetLastError());
   return WHMC_OK;
@@ -405,10 +420,10 @@ whmc_status split_cg(whmc_ctx* c, int prec, int links, int nrhs, void* p, void* 
       TraceRange tr(mixed ? "whmc cg iteration (mixed)" : "whmc cg iteration");
       CGScalars* cur = c->scal;
       CGScalars* nxt = cur == c->scal_base ? c->scal_base + kMaxRhs : c->scal_base;
-      launch_split<0, kCgHop>(c, 0, nrhs, L, P, P, T, P, R, X, 0.0, 0.0, kk, ~0u, cur, pa, pa);
-      launch_split<0, kCgU>(c, 1, nrhs, L, T, P, U, P, R, X, 0.0, 0.0, kk, ~0u, cur, pa, pa);
-      launch_split<1, kCgHop>(c, 0, nrhs, L, U, U, V, U, R, X, 0.0, 0.0, kk, ~0u, cur, pa, pa);
-      launch_split<1, kCgR>(c, 1, nrhs, L, V, U, V, P, R, X, 0.0, 0.0, kk, ~0u, cur, pa, pb);
+      launch_split<0, kCgHop>(c, 0, nrhs, L, P, P, T, P, R, X, 0.0, kk, ~0u, cur, pa, pa);
+      launch_split<0, kCgU>(c, 1, nrhs, L, T, P, U, P, R, X, 0.0, kk, ~0u, cur, pa, pa);
+      launch_split<1, kCgHop>(c, 0, nrhs, L, U, U, V, U, R, X, 0.0, kk, ~0u, cur, pa, pa);
+      launch_split<1, kCgR>(c, 1, nrhs, L, V, U, V, P, R, X, 0.0, kk, ~0u, cur, pa, pb);
       hipLaunchKernelGGL((k_split_p<mixed, S, SR>), dim3(nb * nrhs), dim3(kSplitWG), 0, c->stream, fast_div(nrhs),
                          nrhs, Vh, P, R, cur,
                          nxt, pb, nb);

@@ -75,3 +75,51 @@ def test_solves_match_the_oracle(prec, links, tol, bound, check_every):
         assert st1[0]["converged"] and rel_err(unpack_half(split, one), ref) < bound
     assert st[1]["iters"] == 0 and not got[1].any()
     assert st[0]["iters"] != st[2]["iters"]
+
+
+# M^dag M for several masses in one call against one call each: the
+# direction-split kernels, and the multi-RHS kernels (streamed links make the lattice a large one), with
+# the batches that 19 right-hand sides make
+@pytest.mark.parametrize("eo", [True, False])
+@pytest.mark.parametrize("dims,large,n", [((2, 2, 2, 2), False, 3), ((4, 4, 4, 4), False, 19), ((6, 4, 6, 8), False, 19),
+                                          ((6, 4, 6, 8), True, 7), ((4, 12, 16, 16), True, 5)])
+def test_mdagm_of_several_masses(dims, large, n, eo):
+    lat = Lattice(dims)
+    U, ctx, thread = _pair(dims, 9330)
+    if large:
+        ctx.set_option(whmc.OPT_STREAM_THRESHOLD, 0)
+    kappas = [0.10 + 0.003 * r for r in range(n)]
+    sites, parity = (lat.Vh, 1) if eo else (lat.V, -1)
+    x = ctx.pack_spinor(torch.from_numpy(np.stack([synth.gaussian_spinor(sites, 9331 + r) for r in range(n)])).cuda(), parity)
+    out = ctx.apply_MdagM(x, kappas, eo=eo).chunk(n)
+    for r, one in enumerate(x.chunk(n)):
+        ref = thread.apply_MdagM(one, [kappas[r]], eo=eo)
+        assert float((out[r] - ref).abs().max() / ref.abs().max()) < 1e-14
+        if not large:
+            assert torch.equal(out[r], ref)
+    if not large:
+        noalloc = ctx.apply_MdagM_noalloc(x, kappas, torch.full_like(x, float("nan")), eo=eo)
+        assert torch.equal(noalloc, torch.cat(out))
+
+
+def test_mdagm_under_capture_keeps_to_the_scratch_there_is():
+    dims = (6, 4, 6, 8)
+    _, ctx, _ = _pair(dims, 9340)
+    x = pack_half(ctx, np.stack([synth.gaussian_spinor(ctx.Vh, 9341 + r) for r in range(3)]))
+    ref = [ctx.apply_MdagM(one, [0.12]).clone() for one in x.chunk(3)]   # scratch for one right-hand side
+    stream = torch.cuda.Stream()
+    ctx2 = whmc.Context(dims, stream=stream)
+    with torch.cuda.stream(stream):
+        ctx2.load_gauge(ctx.export_gauge(), unitarity_tol=0.0)
+        ctx2.apply_MdagM(x.chunk(3)[0], [0.12])
+        out = torch.zeros_like(x)
+    stream.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        ctx2.apply_MdagM(x, [0.12] * 3, out=out)
+    for _ in range(3):
+        out.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, torch.cat(ref))
