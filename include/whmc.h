@@ -178,9 +178,8 @@ whmc_status whmc_apply_H(whmc_ctx* ctx, void* out, const void* in, int out_parit
  * Allowed: FP64 (18-, 12- or 8-real links) rhs_block = 1 with rhs_lanes = 1, 2 or 4, or rhs_block = 2
  * with rhs_lanes = 1 or 2; FP32 / FP16 (12- or 8-real links) rhs_block = 1, 2 or 4 with
  * rhs_lanes = 1 or 2; other formats WHMC_EUNSUP.  rhs_block = rhs_lanes = 0
- * takes the autotuned blocking and order (rhs_order ignored), or on small lattices kernels without a
- * blocking; one of them 0 reads as 1; anything
- * else is WHMC_EARG. */
+ * takes the autotuned blocking and order (rhs_order ignored) or, on small lattices and in FP64 and FP32,
+ * kernels without a blocking; one of them 0 reads as 1; anything else is WHMC_EARG. */
 whmc_status whmc_apply_H_multi(whmc_ctx* ctx, void* out, const void* in, int out_parity, int dagger, int prec,
                                int links, int nrhs, int rhs_block, int rhs_lanes, int rhs_order);
 
@@ -240,8 +239,8 @@ typedef struct whmc_cg_params {
   int links;          /* whmc_links of the bulk operator */
   double delta;       /* reliable-update trigger (mixed only), e.g. 0.1 */
   int check_every;    /* iterations enqueued between host convergence checks (>= 1) */
-  int rhs_block;      /* multi-RHS register block (right-hand sides per thread), 0 = autotuned */
-  int rhs_lanes;      /* multi-RHS lanes per site sharing link loads, 0 = autotuned */
+  int rhs_block;      /* multi-RHS register block (right-hand sides per thread), 0 = the library's choice */
+  int rhs_lanes;      /* multi-RHS lanes per site sharing link loads, 0 = the library's choice */
   int rhs_order;      /* multi-RHS workgroup order (see whmc_apply_H_multi); ignored when autotuned */
 } whmc_cg_params;
 

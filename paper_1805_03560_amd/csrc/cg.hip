@@ -60,9 +60,9 @@ __global__ __launch_bounds__(kBlock) void k_cg2(Geom g, Lnk L, S t, S p, S u, do
 }
 
 // pass 2 of kernel 2: (p, A p) -> alpha
-__global__ __launch_bounds__(256) void k_cg2_fin(CGScalars* sc, const double* partials, int nb) {
+__global__ __launch_bounds__(kFinWG) void k_cg2_fin(CGScalars* sc, const double* partials, int nb) {
   if (halted(sc)) return;
-  const double pAp = sum_partials<256>(partials, nb);
+  const double pAp = sum_partials<kFinWG>(partials, nb);
   if (threadIdx.x != 0) return;
   sc->pAp = pAp;
   if (pAp > 0.0 && pAp < INFINITY) {
@@ -120,9 +120,9 @@ __global__ __launch_bounds__(kBlock) void k_cg4(Geom g, Lnk L, S v, S u, S p, SR
 
 // pass 2 of kernel 4: new |r|^2 -> beta, stop / reliable-update tests
 template <bool MIXED>
-__global__ __launch_bounds__(256) void k_cg4_fin(CGScalars* sc, const double* partials, int nb) {
+__global__ __launch_bounds__(kFinWG) void k_cg4_fin(CGScalars* sc, const double* partials, int nb) {
   if (halted(sc)) return;
-  const double rr_new = sum_partials<256>(partials, nb);
+  const double rr_new = sum_partials<kFinWG>(partials, nb);
   if (threadIdx.x != 0) return;
   const double rr_old = sc->rr;
   sc->beta = rr_new / rr_old;
@@ -285,11 +285,11 @@ static whmc_status enqueue_iters(whmc_ctx* c, const Lnk& L, S p, S t, S u, S v, 
     TraceRange tr(MIXED ? "whmc cg iteration (mixed)" : "whmc cg iteration");
     hipLaunchKernelGGL((k_cg1<Lnk, S>), grid, block, lds, c->stream, c->g, L, p, t, c->scal);
     hipLaunchKernelGGL((k_cg2<Lnk, S>), grid, block, lds, c->stream, c->g, L, t, p, u, k2, c->scal, c->red);
-    hipLaunchKernelGGL(k_cg2_fin, dim3(1), dim3(256), 0, c->stream, c->scal, c->red.partials, (int)grid.x);
+    hipLaunchKernelGGL(k_cg2_fin, dim3(1), dim3(kFinWG), 0, c->stream, c->scal, c->red.partials, (int)grid.x);
     hipLaunchKernelGGL((k_cg3<Lnk, S>), grid, block, lds, c->stream, c->g, L, u, v, c->scal);
     hipLaunchKernelGGL((k_cg4<Lnk, S, SR, MIXED>), grid, block, lds, c->stream, c->g, L, v, u, p, r, x, k2, c->scal,
                        c->red);
-    hipLaunchKernelGGL(k_cg4_fin<MIXED>, dim3(1), dim3(256), 0, c->stream, c->scal, c->red.partials, (int)grid.x);
+    hipLaunchKernelGGL(k_cg4_fin<MIXED>, dim3(1), dim3(kFinWG), 0, c->stream, c->scal, c->red.partials, (int)grid.x);
     hipLaunchKernelGGL((k_cg5<S, SR>), grid, block, 0, c->stream, c->Vh, p, r, c->scal);
   }
   WHMC_HIP(hipGetLastError());

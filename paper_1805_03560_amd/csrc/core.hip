@@ -73,7 +73,7 @@ __global__ __launch_bounds__(kBlock) void k_hop(Geom g, int par, Lnk L, SIn in, 
 #pragma unroll
       for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int cc = 0; cc < 3; ++cc) acc.c[s][cc] = R(a) * xv.c[s][cc] + R(b) * acc.c[s][cc];
+        for (int cc = 0; cc < 3; ++cc) acc.c[s][cc] = axpby(R(a), xv.c[s][cc], R(b), acc.c[s][cc]);
     } else {
       scale(acc, b);
     }
@@ -575,7 +575,7 @@ static int reduce_blocks(whmc_ctx* c, long long n) {
   return (int)(b < 1024 ? b : 1024);
 }
 whmc_status finish_sum(whmc_ctx* c, int nparts, double* dev_out) {
-  hipLaunchKernelGGL(k_finish_sum<256>, dim3(1), dim3(256), 0, c->stream, c->red.partials, nparts, dev_out);
+  hipLaunchKernelGGL(k_finish_sum<kFinWG>, dim3(1), dim3(kFinWG), 0, c->stream, c->red.partials, nparts, dev_out);
   WHMC_HIP(hipGetLastError());
   return WHMC_OK;
 }
@@ -831,20 +831,23 @@ whmc_status whmc_apply_Moo(whmc_ctx* c, double* out, const double* in, double ka
 }
 
 // How many of nrhs right-hand sides one pass of M^dag M takes: as many as the direction-split kernels of
-// small lattices allow; on larger lattices the even/odd operator takes up to four through the multi-RHS
-// kernels (57 to 79 us per rhs and hop at 24^3 x 48 against 98, most of it gained by the second; the
-// batch's scratch grows with it) and the full one, whose kernels have no multi-RHS form, one.
+// small lattices allow; where the even/odd operator has the kernels that read each link once for all of
+// them, four, or a total of 524288 sites (the batch's scratch grows with it: 24^3 x 48, one 431 us, two 273
+// each, four 227; 16^3 x 32, one 70, two 52 each, four 41, six 38).
 static int mdagm_batch(const whmc_ctx* c, int nrhs, int eo) {
-  for (int n = std::min(nrhs, kMaxRhs); n >= 1; --n)
-    if (split_hops(c, WHMC_F64, WHMC_L18, eo ? n : 2 * n)) return n;
-  return eo && !c->split_off ? std::min(nrhs, 4) : 1;
+  nrhs = std::min(nrhs, kMaxRhs);
+  if (eo && !c->split_off && !split_hops(c, WHMC_F64, WHMC_L18, nrhs) && sweep_rhs(c, WHMC_F64, WHMC_L18, nrhs))
+    return std::min(nrhs, std::max(4, 524288 / c->Vh));
+  for (int n = nrhs; n > 1; --n)
+    if (eo ? split_hops(c, WHMC_F64, WHMC_L18, n) : split_fits(c, WHMC_F64, WHMC_L18, 2 * n)) return n;
+  return 1;
 }
 
 // out_r = A(kappa_r) in_r for a batch that mdagm_batch chose; w: n * V * 192 bytes
 static whmc_status mdagm_some(whmc_ctx* c, double* out, const double* in, const double* kappas, int n, int eo, double* w) {
   const size_t h = (size_t)24 * c->Vh;
   if (!eo) {
-    if (!split_hops(c, WHMC_F64, WHMC_L18, 2 * n)) return apply_MdagM_full(c, out, in, kappas[0], w);
+    if (!split_fits(c, WHMC_F64, WHMC_L18, 2 * n)) return apply_MdagM_full(c, out, in, kappas[0], w);
     WHMC_TRY(split_fullM(c, 0, n, w, in, kappas));
     return split_fullM(c, 1, n, out, w, kappas);
   }
@@ -858,7 +861,7 @@ static whmc_status mdagm_some(whmc_ctx* c, double* out, const double* in, const 
     WHMC_TRY(split_hop(c, WHMC_F64, WHMC_L18, 0, 1, n, te, to, nullptr, 0.0, one));
     return split_hop(c, WHMC_F64, WHMC_L18, 1, 1, n, out, te, to, 1.0, b);
   }
-  if (n > 1) return apply_MdagM_multi(c, out, in, kappas, n, te, to);
+  if (n > 1) return sweep_mdagm(c, out, in, kappas, n, te, to);
   return apply_MdagM_f64(c, out, in, kappas[0], te, to);
 }
 

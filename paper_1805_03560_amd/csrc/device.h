@@ -39,12 +39,18 @@ template <typename R> WHMC_DEV cplx<R> operator+(cplx<R> a, cplx<R> b) { return 
 template <typename R> WHMC_DEV cplx<R> operator-(cplx<R> a, cplx<R> b) { return {a.re - b.re, a.im - b.im}; }
 template <typename R> WHMC_DEV cplx<R> operator-(cplx<R> a) { return {-a.re, -a.im}; }
 template <typename R> WHMC_DEV cplx<R> operator*(R s, cplx<R> a) { return {s * a.re, s * a.im}; }
+// The fused multiply-adds of products are written out, so that the compiler does not choose which product of
+// a sum it rounds first: kernels that do the same hop in different ways give the same bits.
 template <typename R> WHMC_DEV cplx<R> cmul(cplx<R> a, cplx<R> b) {
-  return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
+  return {fma(-a.im, b.im, a.re * b.re), fma(a.im, b.re, a.re * b.im)};
 }
 // conj(a) * b
 template <typename R> WHMC_DEV cplx<R> cjmul(cplx<R> a, cplx<R> b) {
-  return {a.re * b.re + a.im * b.im, a.re * b.im - a.im * b.re};
+  return {fma(a.im, b.im, a.re * b.re), fma(-a.im, b.re, a.re * b.im)};
+}
+// a x + b y, rounded as the product a x and one fused multiply-add
+template <typename R> WHMC_DEV cplx<R> axpby(R a, cplx<R> x, R b, cplx<R> y) {
+  return {fma(b, y.re, a * x.re), fma(b, y.im, a * x.im)};
 }
 // s + a b, s - a b and s + conj(a) b as chains of fused multiply-adds: four instructions instead of the six
 // of "s + cmul(a, b)", whose product is rounded before the sum
@@ -60,7 +66,7 @@ template <typename R> WHMC_DEV cplx<R> cjmad(cplx<R> a, cplx<R> b, cplx<R> s) {
 template <typename R> WHMC_DEV cplx<R> conj(cplx<R> a) { return {a.re, -a.im}; }
 template <typename R> WHMC_DEV cplx<R> times_i(cplx<R> a) { return {-a.im, a.re}; }
 template <typename R> WHMC_DEV cplx<R> times_mi(cplx<R> a) { return {a.im, -a.re}; }
-template <typename R> WHMC_DEV R norm2(cplx<R> a) { return a.re * a.re + a.im * a.im; }
+template <typename R> WHMC_DEV R norm2(cplx<R> a) { return fma(a.im, a.im, a.re * a.re); }
 
 template <typename R>
 struct Spinor {
@@ -402,10 +408,17 @@ WHMC_DEV size_t aos(int k, int i, int K, int n) {
 }
 
 // ------------------------------------------------------------------ spinor storage
+// load_raw() gives the stored components and the factor that load() multiplies them with; the stencil
+// applies it while it projects (FP16; 1 and not applied otherwise).
 struct SpinorF64 {
   using Real = double;
+  static constexpr bool scaled = false;
   double2* p;
   int stride;
+  WHMC_DEV double load_raw(int i, Spinor<double>& s) const {
+    load(i, s);
+    return 1.0;
+  }
   WHMC_DEV void load(int i, Spinor<double>& s) const {
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
@@ -423,8 +436,13 @@ struct SpinorF64 {
 
 struct SpinorF32 {
   using Real = float;
+  static constexpr bool scaled = false;
   float4* p;
   int stride;
+  WHMC_DEV float load_raw(int i, Spinor<float>& s) const {
+    load(i, s);
+    return 1.f;
+  }
   WHMC_DEV void load(int i, Spinor<float>& s) const {
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
@@ -451,8 +469,9 @@ struct SpinorF16 {
   uint4* p;
   float* scale;
   int stride;
-  WHMC_DEV void load(int i, Spinor<float>& s) const {
-    float sc = scale[i];
+  static constexpr bool scaled = true;
+  WHMC_DEV float load_raw(int i, Spinor<float>& s) const {
+    const float sc = scale[i];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       uint4 v = p[aos(k, i, 3, stride)];
@@ -460,9 +479,17 @@ struct SpinorF16 {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         int comp = 4 * k + j;
-        s.c[comp / 3][comp % 3] = {sc * h2f((unsigned short)(w[j] & 0xffffu)), sc * h2f((unsigned short)(w[j] >> 16))};
+        s.c[comp / 3][comp % 3] = {h2f((unsigned short)(w[j] & 0xffffu)), h2f((unsigned short)(w[j] >> 16))};
       }
     }
+    return sc;
+  }
+  WHMC_DEV void load(int i, Spinor<float>& s) const {
+    const float sc = load_raw(i, s);
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < 3; ++b) s.c[a][b] = sc * s.c[a][b];
   }
   template <bool NT = false>
   WHMC_DEV void store(int i, const Spinor<float>& s) const {
@@ -676,15 +703,24 @@ WHMC_DEV void block_partial(double v, double* partials, int slot) {
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_finish_sum(const double* partials, int n, double* out);
 
-// pass 2 helper: sum of p[0..n) by one block of BLOCK threads in a fixed order; valid in thread 0
+// pass 2 helper: sum of p[0..n) by one block of BLOCK threads in a fixed order; valid in thread 0.  Eight
+// loads are on their way at once: a pass is bound by their latency (8192 partials of a 32^3 x 64 hop:
+// 10.5 us with 256 threads and one load each at a time).
 template <int BLOCK>
 WHMC_DEV double sum_partials(const double* p, int n) {
   __shared__ double lds[BLOCK / 64];
   double t = 0.0;
-  for (int k = threadIdx.x; k < n; k += BLOCK) t += p[k];
+  for (int k0 = threadIdx.x; k0 < n; k0 += 8 * BLOCK) {
+    double v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = k0 + j * BLOCK < n ? p[k0 + j * BLOCK] : 0.0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) t += v[j];
+  }
   __syncthreads();
   return block_sum<BLOCK>(t, lds);
 }
+constexpr int kFinWG = 1024;   // threads of the one-workgroup kernels that finish a reduction
 
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_finish_sum(const double* partials, int n, double* out) {

@@ -76,9 +76,9 @@ __global__ __launch_bounds__(kBlock) void k_fullM_update(Geom g, Lnk L, SpinorF6
   block_partial<kBlock>(nrm, red.partials, blockIdx.x);
 }
 
-__global__ __launch_bounds__(256) void k_full_alpha(CGScalars* sc, const double* partials, int nb) {
+__global__ __launch_bounds__(kFinWG) void k_full_alpha(CGScalars* sc, const double* partials, int nb) {
   if (full_halted(sc)) return;
-  const double pAp = sum_partials<256>(partials, nb);
+  const double pAp = sum_partials<kFinWG>(partials, nb);
   if (threadIdx.x != 0) return;
   sc->pAp = pAp;
   if (pAp > 0.0 && pAp < INFINITY) {
@@ -89,9 +89,9 @@ __global__ __launch_bounds__(256) void k_full_alpha(CGScalars* sc, const double*
   }
 }
 
-__global__ __launch_bounds__(256) void k_full_beta(CGScalars* sc, const double* partials, int nb) {
+__global__ __launch_bounds__(kFinWG) void k_full_beta(CGScalars* sc, const double* partials, int nb) {
   if (full_halted(sc)) return;
-  const double rr_new = sum_partials<256>(partials, nb);
+  const double rr_new = sum_partials<kFinWG>(partials, nb);
   if (threadIdx.x != 0) return;
   sc->beta = rr_new / sc->rr;
   sc->rr_old = sc->rr;
@@ -139,7 +139,7 @@ static void launch_fullM(whmc_ctx* c, const Lnk& L, int dagger, double* out, con
 
 whmc_status apply_M_full(whmc_ctx* c, double* out, const double* in, double kappa, int dagger) {
   WHMC_CHECK(c->gauge_loaded, WHMC_ESTATE, "no gauge field loaded");
-  if (split_hops(c, WHMC_F64, WHMC_L18, 2)) return split_fullM(c, dagger, 1, out, in, &kappa);
+  if (split_fits(c, WHMC_F64, WHMC_L18, 2)) return split_fullM(c, dagger, 1, out, in, &kappa);
   if (c->stream_links(WHMC_F64, WHMC_L18)) launch_fullM(c, LinkF64_18T<true>{c->U18, c->Vh}, dagger, out, in, kappa);
   else launch_fullM(c, LinkF64_18T<false>{c->U18, c->Vh}, dagger, out, in, kappa);
   WHMC_HIP(hipGetLastError());
@@ -217,11 +217,11 @@ static whmc_status cg_full_impl(whmc_ctx* c, const Lnk& L, double* x, const doub
         TraceRange tr("whmc full-lattice cg iteration");
         hipLaunchKernelGGL((k_fullM<0, true, true, Lnk>), grid, block, 0, c->stream, c->g, L, half64(P, Vh, 0),
                            half64(P, Vh, 1), half64(T, Vh, 0), half64(T, Vh, 1), kappa, c->scal, c->red);
-        hipLaunchKernelGGL(k_full_alpha, dim3(1), dim3(256), 0, c->stream, c->scal, c->red.partials, (int)grid.x);
+        hipLaunchKernelGGL(k_full_alpha, dim3(1), dim3(kFinWG), 0, c->stream, c->scal, c->red.partials, (int)grid.x);
         hipLaunchKernelGGL((k_fullM_update<Lnk>), grid, block, 0, c->stream, c->g, L, half64(T, Vh, 0),
                            half64(T, Vh, 1), half64(P, Vh, 0), half64(P, Vh, 1), half64(R, Vh, 0), half64(R, Vh, 1),
                            half64(x, Vh, 0), half64(x, Vh, 1), kappa, c->scal, c->red);
-        hipLaunchKernelGGL(k_full_beta, dim3(1), dim3(256), 0, c->stream, c->scal, c->red.partials, (int)grid.x);
+        hipLaunchKernelGGL(k_full_beta, dim3(1), dim3(kFinWG), 0, c->stream, c->scal, c->red.partials, (int)grid.x);
         hipLaunchKernelGGL(k_full_p, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, n, (double2*)P,
                            (const double2*)R, c->scal);
       }

@@ -172,7 +172,8 @@ whmc_status hop(whmc_ctx* c, int prec, int links, int par, int dag, void* out, c
                 double a, double b, double* norm_out, bool nt_store = false);
 
 // ---- direction-split kernels for small lattices (split.hip)
-bool split_hops(const whmc_ctx* c, int prec, int links, int nrhs);   // whether this call takes them
+bool split_fits(const whmc_ctx* c, int prec, int links, int nrhs);   // whether they beat a thread per site
+bool split_hops(const whmc_ctx* c, int prec, int links, int nrhs);   // whether a hop, M^dag M or CG takes them
 whmc_status split_hop(whmc_ctx* c, int prec, int links, int par, int dag, int nrhs, void* out, const void* in,
                       const void* x, double a, const double* b);   // b[nrhs]
 // out_r = M(kappa_r)^(dag) in_r on nrhs <= kMaxRhs full spinors, FP64 with 18-real links
@@ -184,6 +185,23 @@ whmc_status split_residual(whmc_ctx* c, unsigned mask, int nrhs, const double* x
 // them are in c->scal
 whmc_status split_cg(whmc_ctx* c, int prec, int links, int nrhs, void* p, void* t, void* u, void* v, void* r, void* x,
                      const double* k2, int n);
+
+// ---- several right-hand sides, each link read once for all of them (sweep.hip)
+bool sweep_rhs(const whmc_ctx* c, int prec, int links, int nrhs);   // whether these calls take them (FP64 and FP32)
+int sweep_parts(const whmc_ctx* c);   // partial sums per rhs that the following leave in c->red.partials
+// out_r = H in_r for the right-hand sides in mask that are not stopped or paused (sc, unless null)
+whmc_status sweep_hop(whmc_ctx* c, int prec, int links, int par, int dag, int nrhs, void* out, const void* in,
+                      unsigned mask, const CGScalars* sc);
+// CG steps on the right-hand sides that are not stopped or paused (c->scal), all fields of precision prec:
+// u = p - kappa^2 H_oe t with |u|^2;  A p = u - kappa^2 H_oe^dag v, r -= alpha A p, x += alpha p with |r|^2
+whmc_status sweep_u(whmc_ctx* c, int prec, int links, int nrhs, void* u, const void* t, const void* p, const double* k2);
+whmc_status sweep_r(whmc_ctx* c, int prec, int links, int nrhs, void* r, void* x, const void* v, const void* u,
+                    const void* p, const double* k2);
+// as split_residual, |r_q|^2 as partial sums
+whmc_status sweep_residual(whmc_ctx* c, unsigned mask, int nrhs, const double* x, const double* b, const double* k2,
+                           void* t, void* u, void* v, void* r);
+// out_r = A(kappa_r) in_r, A = M_oo^dag M_oo, FP64 with 18-real links; te, to: nrhs half fields each
+whmc_status sweep_mdagm(whmc_ctx* c, double* out, const double* in, const double* kappas, int nrhs, double* te, double* to);
 
 // ---- FP64 BLAS on half fields (core.hip); n = number of half fields
 whmc_status axpby_f64(whmc_ctx* c, double* y, double a, const double* x, double b, int nhalf);  // y = a x + b y
@@ -205,10 +223,6 @@ whmc_status apply_K_f64(whmc_ctx* c, double* out, const double* in, double kappa
 // full lattice (full spinors = even half, odd half): out = M in or M^dag in, M = 1 - kappa H (full.hip)
 whmc_status apply_M_full(whmc_ctx* c, double* out, const double* in, double kappa, int dagger);
 whmc_status apply_MdagM_full(whmc_ctx* c, double* out, const double* in, double kappa, double* tmp_full);
-
-// out_r = A(kappa_r) in_r, A = M_oo^dag M_oo, through the multi-RHS kernels (multi.hip); te, to: nrhs half fields each
-whmc_status apply_MdagM_multi(whmc_ctx* c, double* out, const double* in, const double* kappas, int nrhs, double* te,
-                              double* to);
 
 // ---- solvers (cg.hip)
 whmc_status cg_solve(whmc_ctx* c, double* x, const double* b, const double* kappas, int nrhs,

@@ -131,7 +131,6 @@ template <int MU, int DAG, int NB, class Lnk, class S, typename R>
 WHMC_DEV void hop_dir_multi(const Geom& g, const Coords& c, int par, int i, const Lnk& L, const S* in,
                             const bool* act, Spinor<R>* acc) {
   constexpr int SF = DAG ? +1 : -1;
-  constexpr int SB = -SF;
   bool wrap;
   SU3<R> U;
   {
@@ -141,12 +140,9 @@ WHMC_DEV void hop_dir_multi(const Geom& g, const Coords& c, int par, int i, cons
     for (int k = 0; k < NB; ++k) {
       if (!act[k]) continue;
       Spinor<R> s;
-      HalfSpinor<R> h, u;
-      in[k].load(j, s);
-      project<MU, SF>(s, h);
-      if (MU == 0 && wrap) negate(h);
-      mul(U, h.c[0], u.c[0]);
-      mul(U, h.c[1], u.c[1]);
+      HalfSpinor<R> u;
+      const R sc = in[k].load_raw(j, s);
+      hop_apply<MU, +1, DAG, S::scaled>(U, s, sc, wrap, u);
       accumulate<MU, SF>(acc[k], u);
     }
   }
@@ -157,13 +153,10 @@ WHMC_DEV void hop_dir_multi(const Geom& g, const Coords& c, int par, int i, cons
     for (int k = 0; k < NB; ++k) {
       if (!act[k]) continue;
       Spinor<R> s;
-      HalfSpinor<R> h, u;
-      in[k].load(j, s);
-      project<MU, SB>(s, h);
-      if (MU == 0 && wrap) negate(h);
-      mul_dag(U, h.c[0], u.c[0]);
-      mul_dag(U, h.c[1], u.c[1]);
-      accumulate<MU, SB>(acc[k], u);
+      HalfSpinor<R> u;
+      const R sc = in[k].load_raw(j, s);
+      hop_apply<MU, -1, DAG, S::scaled>(U, s, sc, wrap, u);
+      accumulate<MU, -SF>(acc[k], u);
     }
   }
 }
@@ -224,8 +217,8 @@ __global__ __launch_bounds__(kBlock) void k_mcg3(Geom g, int G, int order, Lnk L
   mhop_body<1>(g, 0, m, L, u0, v0, live);
 }
 
-// CG kernel 2: u = p - kappa^2 H_oe^(DAG) t, |u|^2 = (p, A p)
-template <int DAG, int NB, int R, class Lnk, class S, class P>
+// CG kernel 2: u = p - kappa^2 H_oe t, |u|^2 = (p, A p)
+template <int NB, int R, class Lnk, class S, class P>
 __global__ __launch_bounds__(kBlock) void k_mcg2(Geom g, int nrhs, int G, int order, Lnk L, S t0, S p0, S u0, K2 k2, P live,
                                                  Reduce red, int nslots) {
   using Re = typename S::Real;
@@ -245,7 +238,7 @@ __global__ __launch_bounds__(kBlock) void k_mcg2(Geom g, int nrhs, int G, int or
     }
     if (any) {
       Spinor<Re> acc[NB];
-      hop_site_multi<DAG, NB>(g, 1, m.i, L, in, act, acc);
+      hop_site_multi<0, NB>(g, 1, m.i, L, in, act, acc);
 #pragma unroll
       for (int k = 0; k < NB; ++k) {
         if (!act[k]) continue;
@@ -265,10 +258,10 @@ __global__ __launch_bounds__(kBlock) void k_mcg2(Geom g, int nrhs, int G, int or
   mpartials<NB, R>(nrm, red.partials, m, nrhs, nslots);
 }
 
-__global__ __launch_bounds__(256) void k_mcg2_fin(CGScalars* sc, int nrhs, const double* partials, int nb) {
+__global__ __launch_bounds__(kFinWG) void k_mcg2_fin(CGScalars* sc, int nrhs, const double* partials, int nb) {
   const int r = blockIdx.x;
   if (!rhs_live(sc, r, nrhs)) return;
-  const double pAp = sum_partials<256>(partials + (size_t)r * nb, nb);
+  const double pAp = sum_partials<kFinWG>(partials + (size_t)r * nb, nb);
   if (threadIdx.x != 0) return;
   sc[r].pAp = pAp;
   if (pAp > 0.0 && pAp < INFINITY) {
@@ -336,10 +329,10 @@ __global__ __launch_bounds__(kBlock) void k_mcg4(Geom g, int nrhs, int G, int or
 }
 
 template <bool MIXED>
-__global__ __launch_bounds__(256) void k_mcg4_fin(CGScalars* sc, int nrhs, const double* partials, int nb) {
+__global__ __launch_bounds__(kFinWG) void k_mcg4_fin(CGScalars* sc, int nrhs, const double* partials, int nb) {
   const int r = blockIdx.x;
   if (!rhs_live(sc, r, nrhs)) return;
-  const double rr_new = sum_partials<256>(partials + (size_t)r * nb, nb);
+  const double rr_new = sum_partials<kFinWG>(partials + (size_t)r * nb, nb);
   if (threadIdx.x != 0) return;
   CGScalars& q = sc[r];
   const double rr_old = q.rr;
@@ -386,10 +379,10 @@ __global__ __launch_bounds__(kBlock) void k_mres(Geom g, int nrhs, int G, int or
 }
 
 // pass 2 of k_mres: out[r] = |r_r|^2 for the chosen right-hand sides
-__global__ __launch_bounds__(256) void k_mres_fin(BySet live, const double* partials, int nb, double* out) {
+__global__ __launch_bounds__(kFinWG) void k_mres_fin(BySet live, const double* partials, int nb, double* out) {
   const int r = blockIdx.x;
   if (!live(r)) return;
-  const double rr = sum_partials<256>(partials + (size_t)r * nb, nb);
+  const double rr = sum_partials<kFinWG>(partials + (size_t)r * nb, nb);
   if (threadIdx.x == 0) out[r] = rr;
 }
 
@@ -714,18 +707,39 @@ static void enqueue_multi(whmc_ctx* c, int nrhs, int order, const Lnk& L, S p, S
   for (int it = 0; it < n; ++it) {
     TraceRange tr("whmc multi-rhs cg iteration");
     hipLaunchKernelGGL((k_mcg1<NB, R, Lnk, S, ByScalars>), grid, block, 0, c->stream, c->g, G, order, L, p, t, live);
-    hipLaunchKernelGGL((k_mcg2<0, NB, R, Lnk, S, ByScalars>), grid, block, 0, c->stream, c->g, nrhs, G, order, L, t, p, u,
+    hipLaunchKernelGGL((k_mcg2<NB, R, Lnk, S, ByScalars>), grid, block, 0, c->stream, c->g, nrhs, G, order, L, t, p, u,
                        k2,
                        live, c->red, ns);
-    hipLaunchKernelGGL(k_mcg2_fin, dim3(nrhs), dim3(256), 0, c->stream, c->scal, nrhs, c->red.partials, ns * R);
+    hipLaunchKernelGGL(k_mcg2_fin, dim3(nrhs), dim3(kFinWG), 0, c->stream, c->scal, nrhs, c->red.partials, ns * R);
     hipLaunchKernelGGL((k_mcg3<NB, R, Lnk, S, ByScalars>), grid, block, 0, c->stream, c->g, G, order, L, u, v, live);
     hipLaunchKernelGGL((k_mcg4<NB, R, Lnk, S, SR, MIXED>), grid, block, 0, c->stream, c->g, nrhs, G, order, L, v, u, p,
                        r, x,
                        k2, c->scal, c->red, ns);
-    hipLaunchKernelGGL(k_mcg4_fin<MIXED>, dim3(nrhs), dim3(256), 0, c->stream, c->scal, nrhs, c->red.partials,
+    hipLaunchKernelGGL(k_mcg4_fin<MIXED>, dim3(nrhs), dim3(kFinWG), 0, c->stream, c->scal, nrhs, c->red.partials,
                        ns * R);
     hipLaunchKernelGGL((k_mcg5<S, SR>), grid5, block, 0, c->stream, c->Vh, nrhs, p, r, c->scal);
   }
+}
+
+// The same n iterations through the sweep kernels (FP64 or FP32 throughout).
+template <class S>
+static whmc_status enqueue_sweep(whmc_ctx* c, int prec, int links, int nrhs, S p, S t, S u, S v, S r, S x, const K2& k2,
+                                 int n) {
+  constexpr bool mixed = std::is_same<S, SpinorF32>::value;
+  const dim3 grid5(c->num_blocks(), nrhs), block(kBlock);
+  double* part = c->red.partials;
+  const int np = sweep_parts(c);
+  for (int it = 0; it < n; ++it) {
+    TraceRange tr("whmc multi-rhs cg iteration");
+    WHMC_TRY(sweep_hop(c, prec, links, 0, 0, nrhs, t.p, p.p, ~0u, c->scal));
+    WHMC_TRY(sweep_u(c, prec, links, nrhs, u.p, t.p, p.p, k2.v));
+    hipLaunchKernelGGL(k_mcg2_fin, dim3(nrhs), dim3(kFinWG), 0, c->stream, c->scal, nrhs, part, np);
+    WHMC_TRY(sweep_hop(c, prec, links, 0, 1, nrhs, v.p, u.p, ~0u, c->scal));
+    WHMC_TRY(sweep_r(c, prec, links, nrhs, r.p, x.p, v.p, u.p, p.p, k2.v));
+    hipLaunchKernelGGL(k_mcg4_fin<mixed>, dim3(nrhs), dim3(kFinWG), 0, c->stream, c->scal, nrhs, part, np);
+    hipLaunchKernelGGL((k_mcg5<S, S>), grid5, block, 0, c->stream, c->Vh, nrhs, p, r, c->scal);
+  }
+  return WHMC_OK;
 }
 
 // r_r = b_r - M_oo(kappa_r)^dag M_oo(kappa_r) x_r for every rhs r in mask, FP64 with 18-real links,
@@ -738,19 +752,26 @@ static void enqueue_residual(whmc_ctx* c, unsigned mask, int nrhs, int order, co
   const dim3 grid(ns * G * R), block(kBlock);
   const BySet live{mask, nrhs};
   hipLaunchKernelGGL((k_mcg1<1, R, Lnk, SpinorF64, BySet>), grid, block, 0, c->stream, c->g, G, order, L, x, t, live);
-  hipLaunchKernelGGL((k_mcg2<0, 1, R, Lnk, SpinorF64, BySet>), grid, block, 0, c->stream, c->g, nrhs, G, order, L, t, x,
+  hipLaunchKernelGGL((k_mcg2<1, R, Lnk, SpinorF64, BySet>), grid, block, 0, c->stream, c->g, nrhs, G, order, L, t, x,
                      u, k2,
                      live, c->red, ns);
   hipLaunchKernelGGL((k_mcg3<1, R, Lnk, SpinorF64, BySet>), grid, block, 0, c->stream, c->g, G, order, L, u, v, live);
   hipLaunchKernelGGL((k_mres<R, Lnk>), grid, block, 0, c->stream, c->g, nrhs, G, order, L, v, u, b, r64, k2, live,
                      c->red,
                      ns);
-  hipLaunchKernelGGL(k_mres_fin, dim3(nrhs), dim3(256), 0, c->stream, live, c->red.partials, ns * R, rr_dev);
+  hipLaunchKernelGGL(k_mres_fin, dim3(nrhs), dim3(kFinWG), 0, c->stream, live, c->red.partials, ns * R, rr_dev);
 }
 
 static whmc_status residual_multi(whmc_ctx* c, unsigned mask, int nrhs, const double* x, const double* b,
                                   const K2& k2, void* t, void* u, void* v, void* r64, double* rr_dev) {
   if (split_hops(c, WHMC_F64, WHMC_L18, nrhs)) return split_residual(c, mask, nrhs, x, b, k2.v, t, u, v, r64, rr_dev);
+  if (sweep_rhs(c, WHMC_F64, WHMC_L18, nrhs)) {
+    WHMC_TRY(sweep_residual(c, mask, nrhs, x, b, k2.v, t, u, v, r64));
+    hipLaunchKernelGGL(k_mres_fin, dim3(nrhs), dim3(kFinWG), 0, c->stream, BySet{mask, nrhs}, c->red.partials,
+                       sweep_parts(c), rr_dev);
+    WHMC_HIP(hipGetLastError());
+    return WHMC_OK;
+  }
   Blocking bk;
   WHMC_TRY(autotune_blocking(c, WHMC_F64, WHMC_L18, nrhs, &bk, nullptr));
   const int Vh = c->Vh;
@@ -766,38 +787,6 @@ static whmc_status residual_multi(whmc_ctx* c, unsigned mask, int nrhs, const do
   const Blocking b1{1, bk.lanes, bk.order};   // the residual kernels hold one rhs per thread
   if (stream_multi(c, WHMC_F64, WHMC_L18, nrhs, b1)) WHMC_TRY(run(LinkF64_18T<true>{c->U18, Vh}));
   else WHMC_TRY(run(LinkF64_18T<false>{c->U18, Vh}));
-  WHMC_HIP(hipGetLastError());
-  return WHMC_OK;
-}
-
-// M_oo^dag M_oo on nrhs >= 2 right-hand sides with two lanes per site (the blocking that wins in FP64 at
-// every size where the single-rhs chain is the alternative): a link is read once for two of them.
-// 24^3 x 48, two rhs: XX
-template <class Lnk>
-static void enqueue_mdagm(whmc_ctx* c, int nrhs, const Lnk& L, SpinorF64 x, SpinorF64 out, const K2& k2, SpinorF64 te,
-                          SpinorF64 to) {
-  constexpr int R = 2;
-  const int G = (nrhs + R - 1) / R, ns = c->stencil_blocks();
-  const dim3 grid(ns * G * R), block(kBlock);
-  const BySet live{~0u, nrhs};
-  hipLaunchKernelGGL((k_mcg1<1, R, Lnk, SpinorF64, BySet>), grid, block, 0, c->stream, c->g, G, 0, L, x, te, live);
-  hipLaunchKernelGGL((k_mcg2<0, 1, R, Lnk, SpinorF64, BySet>), grid, block, 0, c->stream, c->g, nrhs, G, 0, L, te, x, to,
-                     k2, live, c->red, ns);
-  hipLaunchKernelGGL((k_mcg3<1, R, Lnk, SpinorF64, BySet>), grid, block, 0, c->stream, c->g, G, 0, L, to, te, live);
-  hipLaunchKernelGGL((k_mcg2<1, 1, R, Lnk, SpinorF64, BySet>), grid, block, 0, c->stream, c->g, nrhs, G, 0, L, te, to,
-                     out, k2, live, c->red, ns);
-}
-
-whmc_status apply_MdagM_multi(whmc_ctx* c, double* out, const double* in, const double* kappas, int nrhs, double* te,
-                              double* to) {
-  K2 k2{};
-  for (int r = 0; r < nrhs; ++r) k2.v[r] = kappas[r] * kappas[r];
-  const int Vh = c->Vh;
-  if (stream_multi(c, WHMC_F64, WHMC_L18, nrhs, Blocking{1, 2, 0}))
-    enqueue_mdagm(c, nrhs, LinkF64_18T<true>{c->U18, Vh}, h64((void*)in, Vh), h64(out, Vh), k2, h64(te, Vh), h64(to, Vh));
-  else
-    enqueue_mdagm(c, nrhs, LinkF64_18T<false>{c->U18, Vh}, h64((void*)in, Vh), h64(out, Vh), k2, h64(te, Vh),
-                  h64(to, Vh));
   WHMC_HIP(hipGetLastError());
   return WHMC_OK;
 }
@@ -825,10 +814,12 @@ whmc_status cg_solve_multi(whmc_ctx* c, double* x, const double* b, const double
   const size_t sb = field_bytes(prec, Vh);
   const int rprec = mixed ? WHMC_F32 : WHMC_F64;
   const size_t rb = field_bytes(rprec, Vh);
-  // the direction-split kernels of small lattices, unless the caller asks for a blocking
-  const bool split = prm->rhs_block <= 0 && prm->rhs_lanes <= 0 && split_hops(c, prec, links, nrhs);
+  // the direction-split kernels, unless the caller asks for a blocking
+  const bool free = prm->rhs_block <= 0 && prm->rhs_lanes <= 0;
+  const bool split = free && split_hops(c, prec, links, nrhs);
+  const bool sweep = free && !split && sweep_rhs(c, prec, links, nrhs);
   Blocking bk{1, 1, 0};
-  if (!split)
+  if (!split && !sweep)
     WHMC_TRY(resolve_blocking(c, prec, links, nrhs, prm->rhs_block, prm->rhs_lanes, prm->rhs_order, &bk));
   void *p, *t, *u, *v, *rs, *xs, *r64, *ft, *fu, *fv;
   WHMC_TRY(workspace(c, "m_p", sb * nrhs, &p));
@@ -882,6 +873,12 @@ whmc_status cg_solve_multi(whmc_ctx* c, double* x, const double* b, const double
     int max_iter_seen = 0;
     while (true) {
       if (split) WHMC_TRY(split_cg(c, prec, links, nrhs, p, t, u, v, rs, xs, k2.v, check));
+      else if (sweep && mixed)
+        WHMC_TRY(enqueue_sweep(c, prec, links, nrhs, h32(p, Vh), h32(t, Vh), h32(u, Vh), h32(v, Vh), h32(rs, Vh),
+                               h32(xs, Vh), k2, check));
+      else if (sweep)
+        WHMC_TRY(enqueue_sweep(c, prec, links, nrhs, h64(p, Vh), h64(t, Vh), h64(u, Vh), h64(v, Vh), h64(rs, Vh),
+                               h64(xs, Vh), k2, check));
       else WHMC_TRY(with_format(c, prec, links, stream_multi(c, prec, links, nrhs, bk), [&](auto L, auto mk) {
         return with_blocking<decltype(L)>(bk, [&](auto nbc, auto lanes) {
           constexpr int NB = decltype(nbc)::value, R = decltype(lanes)::value;
@@ -1017,6 +1014,8 @@ extern "C" whmc_status whmc_apply_H_multi(whmc_ctx* c, void* out, const void* in
     for (double& v : ones) v = 1.0;
     return split_hop(c, prec, links, out_parity, dagger ? 1 : 0, nrhs, out, in, nullptr, 0.0, ones);
   }
+  if (rhs_block <= 0 && rhs_lanes <= 0 && split_format(prec, links) && sweep_rhs(c, prec, links, nrhs))
+    return sweep_hop(c, prec, links, out_parity, dagger ? 1 : 0, nrhs, out, in, ~0u, nullptr);
   Blocking b;
   WHMC_TRY(resolve_blocking(c, prec, links, nrhs, rhs_block, rhs_lanes, rhs_order, &b));
   return mhop(c, prec, links, out_parity, dagger ? 1 : 0, nrhs, b, out, in);

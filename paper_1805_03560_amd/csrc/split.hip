@@ -19,103 +19,9 @@
 #include <type_traits>
 
 #include "internal.h"
-#include "stencil.h"
+#include "split.h"
 
 namespace whmc {
-
-constexpr int kSplitSites = 64, kSplitWG = 512;
-// LDS row of a component: 64 sites and 4 entries of padding, so that the two component pairs that
-// lanes 0..7 and 8..15 read in one cycle (F32) fall into different banks
-constexpr int kSplitRow = kSplitSites + 4;
-
-// ------------------------------------------------------------------ two components of a site
-// pair q (0..5) is components 2q and 2q + 1 in every storage format
-WHMC_DEV void load2(const SpinorF64& f, int i, int q, cplx<double>* v) {
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const double2 w = f.p[aos(2 * q + j, i, 12, f.stride)];
-    v[j] = {w.x, w.y};
-  }
-}
-WHMC_DEV void load2(const SpinorF32& f, int i, int q, cplx<float>* v) {
-  const float4 w = f.p[aos(q, i, 6, f.stride)];
-  v[0] = {w.x, w.y};
-  v[1] = {w.z, w.w};
-}
-WHMC_DEV void load2(const SpinorF16& f, int i, int q, cplx<float>* v) {
-  const uint2 w = ((const uint2*)(f.p + aos(q >> 1, i, 3, f.stride)))[q & 1];
-  const float sc = f.scale[i];
-  v[0] = {sc * h2f((unsigned short)(w.x & 0xffffu)), sc * h2f((unsigned short)(w.x >> 16))};
-  v[1] = {sc * h2f((unsigned short)(w.y & 0xffffu)), sc * h2f((unsigned short)(w.y >> 16))};
-}
-// called by all 64 lanes of a wavefront (lane = 8 q + site % 8); only active lanes store
-WHMC_DEV void store2(const SpinorF64& f, int i, int q, bool act, const cplx<double>* v) {
-  if (!act) return;
-#pragma unroll
-  for (int j = 0; j < 2; ++j) f.p[aos(2 * q + j, i, 12, f.stride)] = make_double2(v[j].re, v[j].im);
-}
-WHMC_DEV void store2(const SpinorF32& f, int i, int q, bool act, const cplx<float>* v) {
-  if (act) f.p[aos(q, i, 6, f.stride)] = make_float4(v[0].re, v[0].im, v[1].re, v[1].im);
-}
-WHMC_DEV void store2(const SpinorF16& f, int i, int q, bool act, const cplx<float>* v) {
-  float m = act ? fmaxf(fmaxf(fabsf(v[0].re), fabsf(v[0].im)), fmaxf(fabsf(v[1].re), fabsf(v[1].im))) : 0.f;
-#pragma unroll
-  for (int off = 8; off < 64; off <<= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-  if (!act) return;
-  const float inv = m > 0.f ? 1.0f / m : 0.f;
-  if (q == 0) f.scale[i] = m;
-  uint2 w;
-  w.x = (unsigned int)f2h(inv * v[0].re) | ((unsigned int)f2h(inv * v[0].im) << 16);
-  w.y = (unsigned int)f2h(inv * v[1].re) | ((unsigned int)f2h(inv * v[1].im) << 16);
-  ((uint2*)(f.p + aos(q >> 1, i, 3, f.stride)))[q & 1] = w;
-}
-
-// sum over the eight directions of components 2q, 2q + 1 of the site in column s (accumulate())
-template <int DAG, typename R>
-WHMC_DEV void gather2(const cplx<R> (*u)[6][kSplitRow], int q, int s, cplx<R>* acc) {
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int k = 2 * q + j, sp = k / 3;
-    const bool up = k < 6;
-    const int same = up ? k : k - 6;                        // spin s - 2 of the half spinor
-    const int swap = up ? k : (3 - sp) * 3 + (k - 3 * sp);  // the other spin
-    cplx<R> a = {R(0), R(0)};
-#pragma unroll
-    for (int d = 0; d < 8; ++d) {
-      const int mu = d >> 1;
-      const R sg = ((d & 1) == 0) == (DAG != 0) ? R(1) : R(-1);
-      const cplx<R> v = u[d][mu == 0 || mu == 3 ? same : swap][s];
-      const R f = up ? R(1) : (mu >= 2 && sp == 3 ? -sg : sg);
-      const bool rot = (mu & 1) && !up;   // times i
-      a.re += f * (rot ? -v.im : v.re);
-      a.im += f * (rot ? v.re : v.im);
-    }
-    acc[j] = a;
-  }
-}
-
-// sum over the workgroup in a fixed order, valid in every thread after the barrier in between
-WHMC_DEV void wave_total(double v, double* lds) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
-}
-WHMC_DEV double add_waves(const double* lds) {
-  double s = 0.0;
-#pragma unroll
-  for (int w = 0; w < kSplitWG / 64; ++w) s += lds[w];
-  return s;
-}
-// this thread's share of one rhs's partial sums
-WHMC_DEV double my_partials(const double* p, int n) {
-  double t = 0.0;
-  for (int k = threadIdx.x; k < n; k += kSplitWG) t += p[k];
-  return t;
-}
-
-struct SplitK2 {
-  double v[kMaxRhs];
-};
 
 // keeps the loads of these kernel arguments above the first branch, so that they wait for memory once
 // together instead of once per branch
@@ -149,48 +55,48 @@ __global__ __launch_bounds__(kSplitWG) void k_split(FastDiv by_nrhs, int nrhs, u
   if (MODE == kFullM) par = r & 1;
   const double rr_cur = MODE == kCgR ? sc[r].rr : 0.0;
   if (cg && (!((mask >> r) & 1u) || (sc && (sc[r].done | sc[r].pause)))) return;
-  __shared__ cplx<R> lds[8][6][kSplitRow];
+  __shared__ cplx<R> lds[8][6][kSplitSites];
   __shared__ double lred[kSplitWG / 64], lsum[kSplitWG / 64];
+  __shared__ float lmax[std::is_same<S, SpinorF16>::value ? 6 : 1][kSplitSites];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const double part = MODE == kCgR ? my_partials(part_in + (size_t)r * nb, nb) : 0.0;
-  const int i = sb * kSplitSites + lane;
-  // the thread's component pair in the second half: pair q of the wavefront's eight sites
-  const int q = lane >> 3, s2 = wave * 8 + (lane & 7), i2 = sb * kSplitSites + s2;
-  const bool act = q < 6 && i2 < g.Vh;
+  // lanes past the last site work on it and store nothing
+  const bool here = sb * kSplitSites + lane < g.Vh;
+  const int i = here ? sb * kSplitSites + lane : g.Vh - 1;
+  // second half: wavefront q < 6 has the component pair q of the same sites
+  const int q = wave;
+  const bool act = q < 6 && here;
+  const At a2 = at(in0, i), b2 = at(r0, i);
   cplx<R> xv[2], pv[2];
   cplx<RR> rv[2], xsv[2];
-  if (i < g.Vh) {
+  {
     const Coords c = coords_of(g, i, par);
-    const S in = field(in0, MODE == kFullM ? r ^ 1 : r);
+    bool wrap = false;
+    Spinor<R> s;
+    SU3<R> U;
     HalfSpinor<R> u;
-    switch (wave) {
-      case 0: hop_half<0, +1, DAG>(g, c, par, i, L, in, u); break;
-      case 1: hop_half<0, -1, DAG>(g, c, par, i, L, in, u); break;
-      case 2: hop_half<1, +1, DAG>(g, c, par, i, L, in, u); break;
-      case 3: hop_half<1, -1, DAG>(g, c, par, i, L, in, u); break;
-      case 4: hop_half<2, +1, DAG>(g, c, par, i, L, in, u); break;
-      case 5: hop_half<2, -1, DAG>(g, c, par, i, L, in, u); break;
-      case 6: hop_half<3, +1, DAG>(g, c, par, i, L, in, u); break;
-      default: hop_half<3, -1, DAG>(g, c, par, i, L, in, u); break;
-    }
+    const int j = neighbour_d(g, c, wave, wrap);
+    const R sc_in = load_site(field(in0, MODE == kFullM ? r ^ 1 : r), at(in0, j), s);
+    L.load(par ^ (wave & 1), wave >> 1, wave & 1 ? j : i, U);
+    hop_apply_d<DAG, S::scaled>(wave, U, s, sc_in, wrap, u);
 #pragma unroll
     for (int k = 0; k < 6; ++k) lds[wave][k][lane] = u.c[k / 3][k % 3];
   }
   // the epilogue's vectors, on their way while the workgroup meets (before the hop they would hold its
   // registers: 142 VGPRs in FP64, one
   // workgroup per compute unit: 14.1 against 11.3 us for the last step at 12^3x24)
-  if (MODE != kPlain && MODE != kCgHop && act) load2(field(x0, r), i2, q, xv);
-  if ((MODE == kCgR || MODE == kRes) && act) load2(field(p0, r), i2, q, pv);
+  if (MODE != kPlain && MODE != kCgHop && act) load2(field(x0, r), a2, q, xv);
+  if ((MODE == kCgR || MODE == kRes) && act) load2(field(p0, r), a2, q, pv);
   if (MODE == kCgR && act) {
-    load2(field(r0, r), i2, q, rv);
-    load2(field(xs0, r), i2, q, xsv);
+    load2(field(r0, r), b2, q, rv);
+    load2(field(xs0, r), b2, q, xsv);
   }
   if (MODE == kCgR) wave_total(part, lsum);
   __syncthreads();
   double nrm = 0.0;
   cplx<R> acc[2];
-  if (act) gather2<DAG>(lds, q, s2, acc);
+  if (act) gather2<DAG>(lds, q, lane, acc);
   if (MODE == kCgR) {
     const double pAp = add_waves(lsum);
     const bool ok = pAp > 0.0 && pAp < INFINITY;   // else a breakdown: p = 0 or not finite
@@ -211,20 +117,30 @@ __global__ __launch_bounds__(kSplitWG) void k_split(FastDiv by_nrhs, int nrhs, u
       }
       nrm = double(norm2(rv[0]) + norm2(rv[1]));
     }
-    store2(field(r0, r), i2, q, act && ok, rv);
-    store2(field(xs0, r), i2, q, act && ok, xsv);
+    if (act && ok) {
+      store2(field(r0, r), b2, q, rv, 0.f);
+      store2(field(xs0, r), b2, q, xsv, 0.f);
+    }
   } else {
     if (act) {
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         if (MODE == kPlain) acc[j] = kk * acc[j];
-        if (MODE == kXpay) acc[j] = R(a) * xv[j] + kk * acc[j];
+        if (MODE == kXpay) acc[j] = axpby(R(a), xv[j], kk, acc[j]);
         if (MODE == kCgU || MODE == kFullM) acc[j] = xv[j] - kk * acc[j];
         if (MODE == kRes) acc[j] = pv[j] - (xv[j] - kk * acc[j]);
       }
       if (MODE == kCgU || MODE == kRes) nrm = double(norm2(acc[0]) + norm2(acc[1]));
     }
-    store2(field(out0, r), i2, q, act, acc);
+    float m = 0.f;
+    if (std::is_same<S, SpinorF16>::value) {
+      if (act) lmax[q][lane] = pair_max(acc);
+      __syncthreads();
+      if (act)
+#pragma unroll
+        for (int k = 0; k < 6; ++k) m = fmaxf(m, lmax[k][lane]);
+    }
+    if (act) store2(field(out0, r), a2, q, acc, m);
   }
   if (MODE == kCgU || MODE == kCgR || MODE == kRes) {
     wave_total(nrm, lred);
@@ -254,15 +170,18 @@ __global__ __launch_bounds__(kSplitWG) void k_split_p(FastDiv by_nrhs, int nrhs,
     }
     return;
   }
-  const int lane = threadIdx.x & 63, q = lane >> 3, i = sb * kSplitSites + (threadIdx.x >> 6) * 8 + (lane & 7);
+  const int lane = threadIdx.x & 63, i = sb * kSplitSites + lane;
+  const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const bool act = q < 6 && i < Vh;
+  const At ap = at(p0, i), ar = at(r0, i);
   cplx<R> pv[2];
   cplx<typename SR::Real> rv[2];
   if (act) {
-    load2(field(p0, r), i, q, pv);
-    load2(field(r0, r), i, q, rv);
+    load2(field(p0, r), ap, q, pv);
+    load2(field(r0, r), ar, q, rv);
   }
   __shared__ double lsum[kSplitWG / 64];
+  __shared__ float lmax[std::is_same<S, SpinorF16>::value ? 6 : 1][kSplitSites];
   wave_total(my_partials(part + (size_t)r * nb, nb), lsum);
   __syncthreads();
   const double rr = add_waves(lsum);
@@ -285,7 +204,15 @@ __global__ __launch_bounds__(kSplitWG) void k_split_p(FastDiv by_nrhs, int nrhs,
       pv[j].im = R(rv[j].im) + R(beta) * pv[j].im;
     }
   }
-  store2(field(p0, r), i, q, act, pv);
+  float m = 0.f;
+  if (std::is_same<S, SpinorF16>::value) {
+    if (act) lmax[q][lane] = pair_max(pv);
+    __syncthreads();
+    if (act)
+#pragma unroll
+      for (int k = 0; k < 6; ++k) m = fmaxf(m, lmax[k][lane]);
+  }
+  if (act) store2(field(p0, r), ap, q, pv, m);
 }
 
 // ------------------------------------------------------------------ host side
@@ -316,21 +243,29 @@ static whmc_status with_links(whmc_ctx* c, int prec, int links, F&& f) {
 
 static int split_blocks(const whmc_ctx* c) { return (c->Vh + kSplitSites - 1) / kSplitSites; }
 
-// Which calls take these kernels: lattices whose one-thread-per-site grid leaves SIMDs idle or with a
+// Which calls gain from these kernels: lattices whose one-thread-per-site grid leaves SIMDs idle or with a
 // single wavefront, as long as the workgroups are few enough that reading a link once per right-hand side
 // (from L2) and the spinors of a 64-site block without the 128-site slice schedule costs less than the
 // idle SIMDs.  us per CG iteration, one thread per site -> split: 8^4 FP64 39.6 -> 30.7, 12^3x24 FP64
-// 52.5 -> 42.8, two rhs FP32 58.1 -> 45.2 and FP16 63.1 -> 48.4, 16^3x32 two rhs FP64 162 -> 144,
+// 52.5 -> 42.8, two rhs FP32 58.1 -> 43.6 and FP16 63.1 -> 44.0, 16^3x32 two rhs FP64 157 -> 141,
 // 16^3x20x40 two rhs FP32 147 -> 126; beyond the lines: 16^3x32 two rhs FP16 81 -> 84, 12-rhs hops at
 // 16^3x32 FP64 129 -> 139 and FP16 39 -> 53, 20^3x40 one rhs FP64 250 -> 271.  FP16 has the least work
 // per site, so its line lies at a total of output sites; FP64 and FP32 have one for the lattice and FP64
 // one for the total.  A schedule or cap that the caller sets selects the one-thread-per-site kernels,
 // which it is about, and so do streamed links.
-bool split_hops(const whmc_ctx* c, int prec, int links, int nrhs) {
+bool split_fits(const whmc_ctx* c, int prec, int links, int nrhs) {
   if (c->split_off || c->stream_links(prec, links)) return false;
   const long long total = (long long)c->Vh * nrhs;
   if (prec == WHMC_F16) return total <= 98304;
   return c->Vh <= 131072 && (prec == WHMC_F32 || total <= 524288);
+}
+
+// ... and which of them take them where the sweep kernels can have the call too: FP64 on two right-hand sides
+// (16^4: 79 us per CG iteration against 84, 16^3 x 40: 174 against 178; on three 107 against 104 and 255
+// against 237).  The line of FP32 is in sweep_rhs.
+bool split_hops(const whmc_ctx* c, int prec, int links, int nrhs) {
+  if (!split_fits(c, prec, links, nrhs)) return false;
+  return !sweep_rhs(c, prec, links, nrhs) || (prec == WHMC_F64 && nrhs == 2);
 }
 
 template <int DAG, int MODE, class Lnk, class S, class SR>
@@ -377,10 +312,10 @@ whmc_status split_fullM(whmc_ctx* c, int dag, int nrhs, double* out, const doubl
 }
 
 // sum of nb partials of each rhs in mask, one workgroup per rhs
-__global__ __launch_bounds__(256) void k_split_sum(unsigned mask, const double* part, int nb, double* out) {
+__global__ __launch_bounds__(kFinWG) void k_split_sum(unsigned mask, const double* part, int nb, double* out) {
   const int r = blockIdx.x;
   if (!((mask >> r) & 1u)) return;
-  const double t = sum_partials<256>(part + (size_t)r * nb, nb);
+  const double t = sum_partials<kFinWG>(part + (size_t)r * nb, nb);
   if (threadIdx.x == 0) out[r] = t;
 }
 
@@ -396,7 +331,7 @@ whmc_status split_residual(whmc_ctx* c, unsigned mask, int nrhs, const double* x
   launch_split<0, kCgU>(c, 1, nrhs, L, T, X, U, X, R, R, 0.0, kk, mask, nullptr, pa, pa);
   launch_split<1, kCgHop>(c, 0, nrhs, L, U, U, V, U, R, R, 0.0, kk, mask, nullptr, pa, pa);
   launch_split<1, kRes>(c, 1, nrhs, L, V, U, R, B, R, R, 0.0, kk, mask, nullptr, pa, pa);
-  hipLaunchKernelGGL(k_split_sum, dim3(nrhs), dim3(256), 0, c->stream, mask, pa, split_blocks(c), rr_dev);
+  hipLaunchKernelGGL(k_split_sum, dim3(nrhs), dim3(kFinWG), 0, c->stream, mask, pa, split_blocks(c), rr_dev);
   WHMC_HIP(hipGetLastError());
   return WHMC_OK;
 }

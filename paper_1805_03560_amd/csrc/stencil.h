@@ -12,9 +12,10 @@
 
 namespace whmc {
 
-// h = psi_up + SGN * A_mu psi_down
-template <int MU, int SGN, typename R>
-WHMC_DEV void project(const Spinor<R>& s, HalfSpinor<R>& h) {
+// h = psi_up + SGN * A_mu psi_down; SCALED: both times sc, as two multiply-adds per number whose factor the
+// stored half precision can be directly (the zero keeps the first one a multiply-add)
+template <int MU, int SGN, bool SCALED, typename R>
+WHMC_DEV void project(const Spinor<R>& s, R sc, HalfSpinor<R>& h) {
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     cplx<R> a0, a1;
@@ -22,9 +23,22 @@ WHMC_DEV void project(const Spinor<R>& s, HalfSpinor<R>& h) {
     if (MU == 1) { a0 = times_mi(s.c[3][c]); a1 = times_mi(s.c[2][c]); }
     if (MU == 2) { a0 = -s.c[3][c]; a1 = s.c[2][c]; }
     if (MU == 3) { a0 = times_mi(s.c[2][c]); a1 = times_i(s.c[3][c]); }
-    if (SGN > 0) { h.c[0][c] = s.c[0][c] + a0; h.c[1][c] = s.c[1][c] + a1; }
-    else         { h.c[0][c] = s.c[0][c] - a0; h.c[1][c] = s.c[1][c] - a1; }
+    if (SCALED) {
+      if (SGN < 0) a0 = -a0, a1 = -a1;
+      h.c[0][c] = {fma(sc, a0.re, fma(sc, s.c[0][c].re, R(0))), fma(sc, a0.im, fma(sc, s.c[0][c].im, R(0)))};
+      h.c[1][c] = {fma(sc, a1.re, fma(sc, s.c[1][c].re, R(0))), fma(sc, a1.im, fma(sc, s.c[1][c].im, R(0)))};
+    } else if (SGN > 0) {
+      h.c[0][c] = s.c[0][c] + a0;
+      h.c[1][c] = s.c[1][c] + a1;
+    } else {
+      h.c[0][c] = s.c[0][c] - a0;
+      h.c[1][c] = s.c[1][c] - a1;
+    }
   }
+}
+template <int MU, int SGN, typename R>
+WHMC_DEV void project(const Spinor<R>& s, HalfSpinor<R>& h) {
+  project<MU, SGN, false>(s, R(1), h);
 }
 
 // acc += [u ; SGN * A_mu^dag u]
@@ -52,20 +66,13 @@ template <typename R> WHMC_DEV void negate(HalfSpinor<R>& h) {
 }
 
 // the half spinor that the hop from x + DIR mu contributes to the output site, before accumulate():
-// the projected neighbour times the link (DIR = +1: U_{x,mu}, DIR = -1: U^dag_{x-mu,mu})
-template <int MU, int DIR, int DAG, class Lnk, class SIn, typename R>
-WHMC_DEV void hop_half(const Geom& g, const Coords& c, int par, int i, const Lnk& L, const SIn& in,
-                       HalfSpinor<R>& u) {
+// the projected neighbour s, times sc if SCALED (load_raw), times the link (DIR = +1: U_{x,mu}, DIR = -1:
+// U^dag_{x-mu,mu}); wrap: the hop crosses the time boundary
+template <int MU, int DIR, int DAG, bool SCALED, typename R>
+WHMC_DEV void hop_apply(const SU3<R>& U, const Spinor<R>& s, R sc, bool wrap, HalfSpinor<R>& u) {
   constexpr int SGN = (DIR > 0) == (DAG != 0) ? +1 : -1;
-  bool wrap;
-  Spinor<R> s;
   HalfSpinor<R> h;
-  SU3<R> U;
-  const int j = neighbour<MU, DIR>(g, c, wrap);
-  in.load(j, s);
-  if (DIR > 0) L.load(par, MU, i, U);
-  else L.load(1 - par, MU, j, U);
-  project<MU, SGN>(s, h);
+  project<MU, SGN, SCALED>(s, sc, h);
   if (MU == 0 && wrap) negate(h);
   if (DIR > 0) {
     mul(U, h.c[0], u.c[0]);
@@ -74,6 +81,19 @@ WHMC_DEV void hop_half(const Geom& g, const Coords& c, int par, int i, const Lnk
     mul_dag(U, h.c[0], u.c[0]);
     mul_dag(U, h.c[1], u.c[1]);
   }
+}
+
+template <int MU, int DIR, int DAG, class Lnk, class SIn, typename R>
+WHMC_DEV void hop_half(const Geom& g, const Coords& c, int par, int i, const Lnk& L, const SIn& in,
+                       HalfSpinor<R>& u) {
+  bool wrap;
+  Spinor<R> s;
+  SU3<R> U;
+  const int j = neighbour<MU, DIR>(g, c, wrap);
+  const R sc = in.load_raw(j, s);
+  if (DIR > 0) L.load(par, MU, i, U);
+  else L.load(1 - par, MU, j, U);
+  hop_apply<MU, DIR, DAG, SIn::scaled>(U, s, sc, wrap, u);
 }
 
 // contribution of direction MU (forward and backward) to the output site
