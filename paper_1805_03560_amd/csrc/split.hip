@@ -12,11 +12,12 @@
 //
 // The sums of a CG iteration need no kernels of their own here: the workgroups of the step that uses a
 // sum add up the few partial sums themselves, all in the same order, so an iteration is five launches
-// instead of seven.  What bounds it: at 8^4 the five launches (about 6 us each with their wait for
-// the previous one); at 12^3x24 FP64 the links and spinors, which every kernel reads anew from the
-// Infinity Cache (an XCD's L2 starts a kernel empty: 31 MB counted per hop, 6.7 us, 5.2 TB/s); in FP16
-// the arithmetic and address instructions of a wavefront (about 400).
+// instead of seven, and four where launches are most of it (k_split_ph).  What bounds it: at 8^4 the
+// launches (about 6 us each with their wait for the previous one); at 12^3x24 FP64 the links and spinors,
+// which every kernel reads anew from the Infinity Cache (an XCD's L2 starts a kernel empty: 31 MB counted
+// per hop, 6.7 us, 5.2 TB/s); in FP16 the arithmetic and address instructions of a wavefront (about 400).
 #include <type_traits>
+#include <utility>
 
 #include "internal.h"
 #include "split.h"
@@ -28,6 +29,45 @@ namespace whmc {
 WHMC_DEV void pin(const Geom& g, const void* links, const void* in) {
   asm volatile("" ::"s"(g.L[0]), "s"(g.L[1]), "s"(g.L[2]), "s"(g.L[3]), "s"(g.Vh), "s"(g.Lxh), "s"(g.dx.m), "s"(g.dx.sh),
                "s"(g.dy.m), "s"(g.dy.sh), "s"(g.dz.m), "s"(g.dz.sh), "s"(links), "s"(in));
+}
+
+// s as load_raw() would give it back from a field (the scale is returned), and the store if asked for
+WHMC_DEV double as_stored(const SpinorF64& f, const At& a, Spinor<double>& s, bool store) {
+  if (store)
+#pragma unroll
+    for (int k = 0; k < 12; ++k)
+      *byte_at<double2>(f.p, a.off + k * a.w) = make_double2(s.c[k / 3][k % 3].re, s.c[k / 3][k % 3].im);
+  return 1.0;
+}
+WHMC_DEV float as_stored(const SpinorF32& f, const At& a, Spinor<float>& s, bool store) {
+  if (store)
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      const cplx<float>&v = s.c[(2 * k) / 3][(2 * k) % 3], &w = s.c[(2 * k + 1) / 3][(2 * k + 1) % 3];
+      *byte_at<float4>(f.p, a.off + k * a.w) = make_float4(v.re, v.im, w.re, w.im);
+    }
+  return 1.f;
+}
+WHMC_DEV float as_stored(const SpinorF16& f, const At& a, Spinor<float>& s, bool store) {
+  float m = 0.f;
+#pragma unroll
+  for (int k = 0; k < 12; ++k) m = fmaxf(m, fmaxf(fabsf(s.c[k / 3][k % 3].re), fabsf(s.c[k / 3][k % 3].im)));
+  const float inv = m > 0.f ? 1.0f / m : 0.f;
+  unsigned int w[12];
+#pragma unroll
+  for (int k = 0; k < 12; ++k) {
+    cplx<float>& z = s.c[k / 3][k % 3];
+    const unsigned short re = f2h(inv * z.re), im = f2h(inv * z.im);
+    w[k] = (unsigned int)re | ((unsigned int)im << 16);
+    z = {h2f(re), h2f(im)};
+  }
+  if (store) {
+    *byte_at<float>(f.scale, 4u * (unsigned)a.i) = m;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      *byte_at<uint4>(f.p, a.off + k * a.w) = make_uint4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
+  }
+  return m;
 }
 
 // ------------------------------------------------------------------ kernels
@@ -149,27 +189,47 @@ __global__ __launch_bounds__(kSplitWG) void k_split(FastDiv by_nrhs, int nrhs, u
   }
 }
 
-// p = r + beta p, beta = |r|^2 / |r_old|^2 from the partial sums; every workgroup adds them up in the
-// same order, the first one of a rhs writes the scalars of the next iteration into the other buffer
+// The scalars of the next iteration, written by the first thread of a rhs: as they are for a right-hand side
+// that has stopped or breaks down here (then true) ...
+WHMC_DEV bool beta_halted(const CGScalars* o, CGScalars* n, bool first) {
+  const int halt = o->done | o->pause | o->brk;
+  if (halt && first) {
+    n->rr = o->rr, n->pAp = o->pAp, n->alpha = o->alpha, n->beta = o->beta, n->rr_old = o->rr_old;
+    n->stop_rr = o->stop_rr, n->rmax2 = o->rmax2, n->delta2 = o->delta2;
+    n->done = o->done | o->brk, n->pause = o->pause, n->iter = o->iter, n->active = o->active, n->brk = 0;
+  }
+  return halt;
+}
+// ... or from the new |r|^2;  false: it stops here
+template <bool MIXED>
+WHMC_DEV bool beta_step(const CGScalars* o, CGScalars* n, bool first, double old_rr, double stop_rr, double delta2,
+                        double old_rmax2, double rr, double& beta) {
+  beta = rr / old_rr;
+  const double rmax2 = fmax(old_rmax2, rr);
+  const bool finite = rr < INFINITY;
+  const bool pause = MIXED && finite && (rr <= stop_rr || rr < delta2 * rmax2);
+  const bool done = !finite || (!MIXED && rr <= stop_rr);
+  if (first) {
+    n->rr = rr, n->pAp = o->pAp, n->alpha = o->alpha, n->beta = beta, n->rr_old = old_rr;
+    n->stop_rr = stop_rr, n->rmax2 = MIXED && finite ? rmax2 : old_rmax2, n->delta2 = delta2;
+    n->done = done, n->pause = pause, n->iter = o->iter + 1, n->active = o->active, n->brk = 0;
+  }
+  return !(pause | done);
+}
+
+// out = r + beta p (p where the rhs stops here), beta = |r|^2 / |r_old|^2 from the partial sums; every
+// workgroup adds them up in the same order, the first one of a rhs writes the scalars of the next
+// iteration into the other buffer.  out may be p.
 template <bool MIXED, class S, class SR>
-__global__ __launch_bounds__(kSplitWG) void k_split_p(FastDiv by_nrhs, int nrhs, int Vh, S p0, SR r0, const CGScalars* cur,
-                                                      CGScalars* nxt, const double* part, int nb) {
+__global__ __launch_bounds__(kSplitWG) void k_split_p(FastDiv by_nrhs, int nrhs, int Vh, S p0, S out0, SR r0,
+                                                      const CGScalars* cur, CGScalars* nxt, const double* part, int nb) {
   using R = typename S::Real;
   const int B = xcd_remap(blockIdx.x, gridDim.x);
   const int sb = by_nrhs.div(B), r = B - sb * nrhs;
   const bool first = sb == 0 && threadIdx.x == 0;
   const CGScalars* o = cur + r;
   const double old_rr = o->rr, stop_rr = o->stop_rr, delta2 = o->delta2, old_rmax2 = o->rmax2;
-  const int halt = o->done | o->pause | o->brk;
-  if (halt) {
-    if (first) {
-      CGScalars* n = nxt + r;
-      n->rr = old_rr, n->pAp = o->pAp, n->alpha = o->alpha, n->beta = o->beta, n->rr_old = o->rr_old;
-      n->stop_rr = stop_rr, n->rmax2 = old_rmax2, n->delta2 = delta2;
-      n->done = o->done | o->brk, n->pause = o->pause, n->iter = o->iter, n->active = o->active, n->brk = 0;
-    }
-    return;
-  }
+  if (beta_halted(o, nxt + r, first)) return;
   const int lane = threadIdx.x & 63, i = sb * kSplitSites + lane;
   const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const bool act = q < 6 && i < Vh;
@@ -184,25 +244,17 @@ __global__ __launch_bounds__(kSplitWG) void k_split_p(FastDiv by_nrhs, int nrhs,
   __shared__ float lmax[std::is_same<S, SpinorF16>::value ? 6 : 1][kSplitSites];
   wave_total(my_partials(part + (size_t)r * nb, nb), lsum);
   __syncthreads();
-  const double rr = add_waves(lsum);
-  const double beta = rr / old_rr;
-  const double rmax2 = fmax(old_rmax2, rr);
-  const bool finite = rr < INFINITY;
-  const bool pause = MIXED && finite && (rr <= stop_rr || rr < delta2 * rmax2);
-  const bool done = !finite || (!MIXED && rr <= stop_rr);
-  if (first) {
-    CGScalars* n = nxt + r;
-    n->rr = rr, n->pAp = o->pAp, n->alpha = o->alpha, n->beta = beta, n->rr_old = old_rr;
-    n->stop_rr = stop_rr, n->rmax2 = MIXED && finite ? rmax2 : old_rmax2, n->delta2 = delta2;
-    n->done = done, n->pause = pause, n->iter = o->iter + 1, n->active = o->active, n->brk = 0;
-  }
-  if (pause || done) return;
-  if (act) {
+  double beta;
+  if (beta_step<MIXED>(o, nxt + r, first, old_rr, stop_rr, delta2, old_rmax2, add_waves(lsum), beta)) {
+    if (act) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      pv[j].re = R(rv[j].re) + R(beta) * pv[j].re;
-      pv[j].im = R(rv[j].im) + R(beta) * pv[j].im;
+      for (int j = 0; j < 2; ++j) {
+        pv[j].re = R(rv[j].re) + R(beta) * pv[j].re;
+        pv[j].im = R(rv[j].im) + R(beta) * pv[j].im;
+      }
     }
+  } else if (p0.p == out0.p) {
+    return;
   }
   float m = 0.f;
   if (std::is_same<S, SpinorF16>::value) {
@@ -212,7 +264,76 @@ __global__ __launch_bounds__(kSplitWG) void k_split_p(FastDiv by_nrhs, int nrhs,
 #pragma unroll
       for (int k = 0; k < 6; ++k) m = fmaxf(m, lmax[k][lane]);
   }
-  if (act) store2(field(p0, r), ap, q, pv, m);
+  if (act) store2(field(out0, r), ap, q, pv, m);
+}
+
+// k_split_p and the hop t = H p of the next iteration in one launch.  Each wavefront makes the new p of its
+// neighbours itself, as the fields hold it; wavefront 0, whose neighbours are all the sites of the other
+// parity, once each, stores it.  pout is not p: other workgroups still read that.
+template <bool MIXED, class Lnk, class S, class SR>
+__global__ __launch_bounds__(kSplitWG, 4) void k_split_ph(FastDiv by_nrhs, int nrhs, Geom g, Lnk L, S p0, S pout0, S t0, SR r0,
+                                                       const CGScalars* cur, CGScalars* nxt, const double* part, int nb) {
+  using R = typename S::Real;
+  const int B = xcd_remap(blockIdx.x, gridDim.x);
+  const int sb = by_nrhs.div(B), r = B - sb * nrhs;
+  pin(g, L.p, p0.p);
+  const bool first = sb == 0 && threadIdx.x == 0;
+  const CGScalars* o = cur + r;
+  const double old_rr = o->rr, stop_rr = o->stop_rr, delta2 = o->delta2, old_rmax2 = o->rmax2;
+  if (beta_halted(o, nxt + r, first)) return;
+  __shared__ cplx<R> lds[8][6][kSplitSites];
+  __shared__ double lsum[kSplitWG / 64];
+  __shared__ float lmax[std::is_same<S, SpinorF16>::value ? 6 : 1][kSplitSites];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const double mine = my_partials(part + (size_t)r * nb, nb);
+  const bool here = sb * kSplitSites + lane < g.Vh;
+  const int i = here ? sb * kSplitSites + lane : g.Vh - 1;
+  const int q = wave;
+  const bool act = q < 6 && here;
+  const At a2 = at(t0, i);
+  {
+    const Coords c = coords_of(g, i, 0);
+    bool wrap = false;
+    const int j = neighbour_d(g, c, wave, wrap);
+    const At aj = at(p0, j);
+    Spinor<R> s;
+    Spinor<typename SR::Real> rv;
+    SU3<R> U;
+    HalfSpinor<R> u;
+    const R sc_in = load_site(field(p0, r), aj, s);
+    load_site(field(r0, r), at(r0, j), rv);
+    if (sizeof(R) == 4) L.load(wave & 1, wave >> 1, wave & 1 ? j : i, U);
+    wave_total(mine, lsum);
+    __syncthreads();
+    double beta;
+    const bool live = beta_step<MIXED>(o, nxt + r, first, old_rr, stop_rr, delta2, old_rmax2, add_waves(lsum), beta);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+      cplx<R>& z = s.c[k / 3][k % 3];
+      const cplx<typename SR::Real>& y = rv.c[k / 3][k % 3];
+      if (S::scaled) z = sc_in * z;
+      if (live) z = {R(y.re) + R(beta) * z.re, R(y.im) + R(beta) * z.im};
+    }
+    const R sc = as_stored(field(pout0, r), aj, s, wave == 0 && here);
+    if (!live) return;
+    if (sizeof(R) == 8) L.load(wave & 1, wave >> 1, wave & 1 ? j : i, U);
+    hop_apply_d<0, S::scaled>(wave, U, s, sc, wrap, u);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) lds[wave][k][lane] = u.c[k / 3][k % 3];
+  }
+  __syncthreads();
+  cplx<R> acc[2];
+  if (act) gather2<0>(lds, q, lane, acc);
+  float m = 0.f;
+  if (std::is_same<S, SpinorF16>::value) {
+    if (act) lmax[q][lane] = pair_max(acc);
+    __syncthreads();
+    if (act)
+#pragma unroll
+      for (int k = 0; k < 6; ++k) m = fmaxf(m, lmax[k][lane]);
+  }
+  if (act) store2(field(t0, r), a2, q, acc, m);
 }
 
 // ------------------------------------------------------------------ host side
@@ -336,6 +457,15 @@ whmc_status split_residual(whmc_ctx* c, unsigned mask, int nrhs, const double* x
   return WHMC_OK;
 }
 
+// One launch instead of two for p and the next hop where the launches are most of an iteration: eight
+// wavefronts now make each p, so it is a loss on more work.  us per iteration, two launches -> one:  FP32 8^4
+// 35.8 -> 33.0, 12^3x24 38.0 -> 35.1, 16^4 42.4 -> 39.9, 12^3x24 four rhs 63.5 -> 65.1, 16^3x32 56.0 -> 57.0;
+// FP16 35.5 -> 32.5, 36.9 -> 35.1, 41.1 -> 39.7, 60.0 -> 62.2, 48.5 -> 49.3;  FP64 8^4 26.7 -> 25.9, four rhs
+// 31.1 -> 29.7, 12^3x24 41.0 -> 44.3 (22 of its registers spill).
+static bool fuse_p(const whmc_ctx* c, int prec, int nrhs) {
+  return (long long)c->Vh * nrhs <= (prec == WHMC_F64 ? 8192 : 49152);
+}
+
 whmc_status split_cg(whmc_ctx* c, int prec, int links, int nrhs, void* p, void* t, void* u, void* v, void* r, void* x,
                      const double* k2, int n) {
   SplitK2 kk{};
@@ -351,17 +481,30 @@ whmc_status split_cg(whmc_ctx* c, int prec, int links, int nrhs, void* p, void* 
     using SR = decltype(R);
     double* pa = c->red.partials;                 // (p, A p)
     double* pb = pa + (size_t)kMaxRhs * nb;       // |r|^2
+    // p moves between two fields where its update and the next iteration's first hop are one launch
+    void* other = nullptr;
+    if (n > 1 && fuse_p(c, prec, nrhs) && workspace(c, "split_p", (size_t)Vh * (mixed ? (prec == WHMC_F32 ? 96 : 52) : 192) * nrhs, &other) != WHMC_OK) {
+      (void)hipGetLastError();   // no memory for it: two launches
+      other = nullptr;
+    }
+    S now = P, next = mk(other, Vh);
     for (int it = 0; it < n; ++it) {
       TraceRange tr(mixed ? "whmc cg iteration (mixed)" : "whmc cg iteration");
       CGScalars* cur = c->scal;
       CGScalars* nxt = cur == c->scal_base ? c->scal_base + kMaxRhs : c->scal_base;
-      launch_split<0, kCgHop>(c, 0, nrhs, L, P, P, T, P, R, X, 0.0, kk, ~0u, cur, pa, pa);
-      launch_split<0, kCgU>(c, 1, nrhs, L, T, P, U, P, R, X, 0.0, kk, ~0u, cur, pa, pa);
+      const dim3 grid(nb * nrhs), block(kSplitWG);
+      if (it == 0 || !other) launch_split<0, kCgHop>(c, 0, nrhs, L, now, now, T, now, R, X, 0.0, kk, ~0u, cur, pa, pa);
+      launch_split<0, kCgU>(c, 1, nrhs, L, T, now, U, now, R, X, 0.0, kk, ~0u, cur, pa, pa);
       launch_split<1, kCgHop>(c, 0, nrhs, L, U, U, V, U, R, X, 0.0, kk, ~0u, cur, pa, pa);
-      launch_split<1, kCgR>(c, 1, nrhs, L, V, U, V, P, R, X, 0.0, kk, ~0u, cur, pa, pb);
-      hipLaunchKernelGGL((k_split_p<mixed, S, SR>), dim3(nb * nrhs), dim3(kSplitWG), 0, c->stream, fast_div(nrhs),
-                         nrhs, Vh, P, R, cur,
-                         nxt, pb, nb);
+      launch_split<1, kCgR>(c, 1, nrhs, L, V, U, V, now, R, X, 0.0, kk, ~0u, cur, pa, pb);
+      if (other && it + 1 < n) {
+        hipLaunchKernelGGL((k_split_ph<mixed, decltype(L), S, SR>), grid, block, 0, c->stream, fast_div(nrhs), nrhs, c->g,
+                           L, now, next, T, R, cur, nxt, pb, nb);
+        std::swap(now, next);
+      } else {
+        hipLaunchKernelGGL((k_split_p<mixed, S, SR>), grid, block, 0, c->stream, fast_div(nrhs), nrhs, Vh, now, P, R, cur,
+                           nxt, pb, nb);
+      }
       c->scal = nxt;
     }
     return WHMC_OK;
