@@ -33,28 +33,8 @@ template <typename R> WHMC_DEV void matmul_nd(const SU3<R>& A, const SU3<R>& B, 
       C.e[i][j] = s;
     }
 }
-// C = A^dag B
-template <typename R> WHMC_DEV void matmul_dn(const SU3<R>& A, const SU3<R>& B, SU3<R>& C) {
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      cplx<R> s = cjmul(A.e[0][i], B.e[0][j]);
-      s = s + cjmul(A.e[1][i], B.e[1][j]);
-      s = s + cjmul(A.e[2][i], B.e[2][j]);
-      C.e[i][j] = s;
-    }
-}
 
-// C += A B, C += A B^dag, C += A^dag B
-template <typename R> WHMC_DEV void mad(const SU3<R>& A, const SU3<R>& B, SU3<R>& C) {
-#pragma unroll
-  for (int k = 0; k < 3; ++k)
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int j = 0; j < 3; ++j) C.e[i][j] = cmad(A.e[i][k], B.e[k][j], C.e[i][j]);
-}
+// C += A B^dag, C += A^dag B
 template <typename R> WHMC_DEV void mad_nd(const SU3<R>& A, const SU3<R>& B, SU3<R>& C) {
 #pragma unroll
   for (int k = 0; k < 3; ++k)
