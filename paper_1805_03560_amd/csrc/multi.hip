@@ -13,7 +13,8 @@
 // scalars.  A converged (or paused, in mixed precision) rhs is masked: its threads skip loads,
 // arithmetic and stores while the others keep iterating, and a workgroup whose right-hand sides
 // are all masked exits at once.  R is chosen by the autotuner (timed on first use per precision,
-// link format and N_rhs) unless the caller fixes it.
+// link format and N_rhs) unless the caller fixes it.  Without a blocking from the caller, calls that the
+// direction-split or the sweep kernels do faster go there (split_hops, sweep_rhs).
 #include <chrono>
 #include <cmath>
 #include <string>
