@@ -203,7 +203,11 @@ whmc_status whmc_apply_M(whmc_ctx* ctx, double* out, const double* in, double ka
  *   eo = 1: A = M_oo^dag M_oo on odd-site half fields (even/odd form, Sec. 2.2),
  *   eo = 0: A = M^dag M on full spinors, M = 1 - kappa H (Sec. 1).
  * The nrhs fields are consecutive (half or full fields).  in and out must not overlap.
- * Uses context scratch for the intermediates (allocated on first use). */
+ * Uses context scratch for the intermediates: V * 192 bytes for each right-hand side that a pass works on,
+ * in buffers for 1, 2, 4, 8 or 16 of them (up to max(4, 2^20 / V) for eo = 1 and 2^19 / V for eo = 0), each
+ * made when a call first needs it and kept at its address until whmc_destroy.  A captured call may thus be
+ * replayed whatever is called in between.  While the stream is captured a call makes do with the buffers
+ * there are, of which an earlier call must have made one with the same eo. */
 whmc_status whmc_apply_MdagM(whmc_ctx* ctx, double* out, const double* in, const double* kappas, int nrhs, int eo);
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving

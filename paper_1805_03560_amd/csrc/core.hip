@@ -716,6 +716,8 @@ void whmc_destroy(whmc_ctx* c) {
   if (c->scal_host) (void)hipHostFree(c->scal_host);
   if (c->host_pinned) (void)hipHostFree(c->host_pinned);
   for (auto& kv : c->ws) (void)hipFree(kv.second.first);
+  for (auto& bufs : c->mdm_buf)
+    for (void* b : bufs) (void)hipFree(b);
   delete c;
 }
 
@@ -865,32 +867,44 @@ static whmc_status mdagm_some(whmc_ctx* c, double* out, const double* in, const 
   return apply_MdagM_f64(c, out, in, kappas[0], te, to);
 }
 
+// Scratch of V * 192 bytes for each of *n right-hand sides (batch.h): an even and an odd half field (eo = 1) or
+// a full field (eo = 0).  While the stream is captured, and where there is no memory for a larger buffer, the
+// batch shrinks to a buffer that there is.
+static whmc_status mdagm_scratch(whmc_ctx* c, int eo, int* n, double** w) {
+  const size_t per = (size_t)c->Vh * 384;
+  void** buf = c->mdm_buf[eo];
+  unsigned have = 0;
+  for (int k = 0; k < kBatchClasses; ++k) have |= (buf[k] != nullptr) << k;
+  BatchClass b = batch_class(have, *n, true);
+  if (!buf[b.cls]) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const bool captured = have != 0 && hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone;
+    if (captured) {
+      b = batch_class(have, *n, false);
+    } else if (b.cls > 0 && hipMalloc(&buf[b.cls], per << b.cls) != hipSuccess) {
+      (void)hipGetLastError();
+      buf[b.cls] = nullptr;
+      b = batch_class(have, *n, false);
+    }
+    if (!buf[b.cls]) WHMC_HIP(hipMalloc(&buf[b.cls], per << b.cls));
+  }
+  *n = b.n;
+  *w = (double*)buf[b.cls];
+  return WHMC_OK;
+}
+
 whmc_status whmc_apply_MdagM(whmc_ctx* c, double* out, const double* in, const double* kappas, int nrhs, int eo) {
   WHMC_CHECK(c && out && in && kappas && nrhs >= 1, WHMC_EARG, "whmc_apply_MdagM: bad argument");
   WHMC_CHECK(out != in, WHMC_EARG, "whmc_apply_MdagM: in and out must differ");
   WHMC_CHECK(eo == 0 || eo == 1, WHMC_EARG, "whmc_apply_MdagM: eo must be 0 (full lattice) or 1 (even/odd)");
   WHMC_CHECK(c->gauge_loaded, WHMC_ESTATE, "no gauge field loaded");
-  // a batch's intermediates: an even and an odd half field (eo = 1) or a full field (eo = 0) per rhs
   int done = 0;
   while (done < nrhs) {
     const size_t f = (size_t)(eo ? 24 : 48) * c->Vh;
-    const size_t per = (size_t)c->Vh * 384;
     int n = mdagm_batch(c, nrhs - done, eo);
-    // a larger scratch than there is cannot be had while the stream is captured: take smaller batches then
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    const auto have = c->ws.find("mdm_tmp");
-    if (have != c->ws.end() && have->second.second < n * per &&
-        hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone)
-      n = std::max(1, (int)(have->second.second / per));
-    void* w = nullptr;
-    whmc_status rc = workspace(c, "mdm_tmp", n * per, &w);
-    if (rc == WHMC_EHIP && n > 1) {   // no memory for the batch
-      (void)hipGetLastError();
-      n = 1;
-      rc = workspace(c, "mdm_tmp", per, &w);
-    }
-    WHMC_TRY(rc);
-    WHMC_TRY(mdagm_some(c, out + done * f, in + done * f, kappas + done, n, eo, (double*)w));
+    double* w = nullptr;
+    WHMC_TRY(mdagm_scratch(c, eo, &n, &w));
+    WHMC_TRY(mdagm_some(c, out + done * f, in + done * f, kappas + done, n, eo, w));
     done += n;
   }
   return WHMC_OK;

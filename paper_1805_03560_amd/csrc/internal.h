@@ -11,6 +11,7 @@
 #include <rocprofiler-sdk-roctx/roctx.h>
 
 #include "../../include/whmc.h"
+#include "batch.h"
 #include "device.h"
 #include "occupancy.h"
 
@@ -96,6 +97,7 @@ struct whmc_ctx {
   std::map<std::string, std::pair<void*, size_t>> ws;
   std::map<std::string, std::pair<int, double>> tuned;   // autotuned multi-RHS blockings (16 nb + lanes, us)
   whmc::Reduce red{};
+  void* mdm_buf[2][whmc::kBatchClasses] = {};   // scratch of whmc_apply_MdagM, [eo][size class]
   void* noalloc_scratch = nullptr;   // device address of the static scratch of whmc_apply_MdagM_noalloc
   // two buffers of kMaxRhs entries: the direction-split CG writes the scalars of the next iteration into
   // the other one; scal is the current one
