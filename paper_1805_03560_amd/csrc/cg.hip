@@ -335,11 +335,11 @@ static whmc_status enqueue_iters(whmc_ctx* c, const Lnk& L, S p, S t, S u, S v, 
   return WHMC_OK;
 }
 
-// plain FP64 CG for one right-hand side
+// plain FP64 CG for one right-hand side; links: the format of L
 template <class Lnk>
 static whmc_status cg_f64(whmc_ctx* c, double* x, const double* b, double kappa, const whmc_cg_params* prm,
-                          whmc_cg_stats* st, Lnk L) {
-  const bool split = split_hops(c, WHMC_F64, prm->links, 1);
+                          whmc_cg_stats* st, Lnk L, int links) {
+  const bool split = split_hops(c, WHMC_F64, links, 1);
   const double k2 = kappa * kappa;
   Timer tm;
   const size_t hb = (size_t)c->Vh * 192;
@@ -389,7 +389,7 @@ static whmc_status cg_f64(whmc_ctx* c, double* x, const double* b, double kappa,
     while (true) {
       const int n = std::min(check, prm->maxiter - total - pass_iters);
       if (n <= 0) break;
-      if (split) WHMC_TRY(split_cg(c, WHMC_F64, prm->links, 1, p, t, u, v, r, x, &k2, n));
+      if (split) WHMC_TRY(split_cg(c, WHMC_F64, links, 1, p, t, u, v, r, x, &k2, n));
       else WHMC_TRY((enqueue_iters<Lnk, SpinorF64, SpinorF64, false>(c, L, s64(p, Vh), s64(t, Vh), s64(u, Vh),
                                                                         s64(v, Vh), s64(r, Vh), s64(x, Vh), kappa, n)));
       WHMC_TRY(read_scalars(c, &hs));
@@ -515,15 +515,15 @@ whmc_status cg_solve(whmc_ctx* c, double* x, const double* b, const double* kapp
   if (p->prec == WHMC_F64 && p->links == WHMC_L12) {
     // FP64 arithmetic with 12-real links: the third row is rebuilt in FP64, exact to rounding
     WHMC_TRY(ensure_links(c, WHMC_F64, WHMC_L12));
-    if (c->stream_links(WHMC_F64, WHMC_L12)) rc = cg_f64(c, x, b, kappas[0], p, s, LinkF64_12T<true>{c->U12, Vh});
-    else rc = cg_f64(c, x, b, kappas[0], p, s, LinkF64_12T<false>{c->U12, Vh});
+    if (c->stream_links(WHMC_F64, WHMC_L12)) rc = cg_f64(c, x, b, kappas[0], p, s, LinkF64_12T<true>{c->U12, Vh}, WHMC_L12);
+    else rc = cg_f64(c, x, b, kappas[0], p, s, LinkF64_12T<false>{c->U12, Vh}, WHMC_L12);
   } else if (p->prec == WHMC_F64 && p->links == WHMC_L8) {
     WHMC_TRY(ensure_links(c, WHMC_F64, WHMC_L8));
-    if (c->stream_links(WHMC_F64, WHMC_L8)) rc = cg_f64(c, x, b, kappas[0], p, s, LinkF64_8T<true>{c->U8, Vh});
-    else rc = cg_f64(c, x, b, kappas[0], p, s, LinkF64_8T<false>{c->U8, Vh});
-  } else if (p->prec == WHMC_F64) {
-    if (c->stream_links(WHMC_F64, WHMC_L18)) rc = cg_f64(c, x, b, kappas[0], p, s, LinkF64_18T<true>{c->U18, Vh});
-    else rc = cg_f64(c, x, b, kappas[0], p, s, LinkF64_18T<false>{c->U18, Vh});
+    if (c->stream_links(WHMC_F64, WHMC_L8)) rc = cg_f64(c, x, b, kappas[0], p, s, LinkF64_8T<true>{c->U8, Vh}, WHMC_L8);
+    else rc = cg_f64(c, x, b, kappas[0], p, s, LinkF64_8T<false>{c->U8, Vh}, WHMC_L8);
+  } else if (p->prec == WHMC_F64) {   // any other value of links: 18-real
+    if (c->stream_links(WHMC_F64, WHMC_L18)) rc = cg_f64(c, x, b, kappas[0], p, s, LinkF64_18T<true>{c->U18, Vh}, WHMC_L18);
+    else rc = cg_f64(c, x, b, kappas[0], p, s, LinkF64_18T<false>{c->U18, Vh}, WHMC_L18);
   } else if (p->prec == WHMC_F32) {
     WHMC_TRY(ensure_links(c, WHMC_F32, p->links));
     const bool nt = c->stream_links(WHMC_F32, p->links);
