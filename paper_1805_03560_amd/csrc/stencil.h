@@ -75,11 +75,11 @@ WHMC_DEV void hop_apply(const SU3<R>& U, const Spinor<R>& s, R sc, bool wrap, Ha
   project<MU, SGN, SCALED>(s, sc, h);
   if (MU == 0 && wrap) negate(h);
   if (DIR > 0) {
-    mul(U, h.c[0], u.c[0]);
-    mul(U, h.c[1], u.c[1]);
+    mul<SCALED>(U, h.c[0], u.c[0]);
+    mul<SCALED>(U, h.c[1], u.c[1]);
   } else {
-    mul_dag(U, h.c[0], u.c[0]);
-    mul_dag(U, h.c[1], u.c[1]);
+    mul_dag<SCALED>(U, h.c[0], u.c[0]);
+    mul_dag<SCALED>(U, h.c[1], u.c[1]);
   }
 }
 
@@ -132,7 +132,7 @@ template <typename R> WHMC_DEV double norm2(const Spinor<R>& a) {
 #pragma unroll
   for (int p = 0; p < 4; ++p)
 #pragma unroll
-    for (int c = 0; c < 3; ++c) s = fma(a.c[p][c].im, a.c[p][c].im, fma(a.c[p][c].re, a.c[p][c].re, s));
+    for (int c = 0; c < 3; ++c) s += norm2(a.c[p][c]);
   return double(s);
 }
 
