@@ -40,44 +40,36 @@ template <typename R> WHMC_DEV cplx<R> operator-(cplx<R> a, cplx<R> b) { return 
 template <typename R> WHMC_DEV cplx<R> operator-(cplx<R> a) { return {-a.re, -a.im}; }
 template <typename R> WHMC_DEV cplx<R> operator*(R s, cplx<R> a) { return {s * a.re, s * a.im}; }
 // The fused multiply-adds of products are written out, so that the compiler does not choose which product of
-// a sum it rounds first: kernels that do the same hop in different ways give the same bits.
+// a sum it rounds first: kernels that do the same hop in different ways give the same bits.  Real parts start with
+// the product of the imaginary parts, which is the smaller one where a and b are near unit matrices.
 template <typename R> WHMC_DEV cplx<R> cmul(cplx<R> a, cplx<R> b) {
-  return {fma(-a.im, b.im, a.re * b.re), fma(a.im, b.re, a.re * b.im)};
+  return {fma(a.re, b.re, -(a.im * b.im)), fma(a.im, b.re, a.re * b.im)};
 }
 // conj(a) * b
 template <typename R> WHMC_DEV cplx<R> cjmul(cplx<R> a, cplx<R> b) {
-  return {fma(a.im, b.im, a.re * b.re), fma(-a.im, b.re, a.re * b.im)};
+  return {fma(a.re, b.re, a.im * b.im), fma(a.re, b.im, -(a.im * b.re))};
 }
 // a x + b y, rounded as the product a x and one fused multiply-add
 template <typename R> WHMC_DEV cplx<R> axpby(R a, cplx<R> x, R b, cplx<R> y) {
   return {fma(b, y.re, a * x.re), fma(b, y.im, a * x.im)};
 }
-// s + a b, s - a b and s + conj(a) b, each product rounded at its own size before it is added (six
-// instructions) or, FUSED, as a chain of multiply-adds (four).  A chain rounds more often at the size of the
-// sum, so it is for what is stored in half precision, whose own rounding hides that.
-template <bool FUSED, typename R> WHMC_DEV cplx<R> cmad(cplx<R> a, cplx<R> b, cplx<R> s) {
-  if (!FUSED) return s + cmul(a, b);
-  return {fma(-a.im, b.im, fma(a.re, b.re, s.re)), fma(a.im, b.re, fma(a.re, b.im, s.im))};
+// a0 b0 + a1 b1 (+ a2 b2) as one chain of multiply-adds, eight (twelve) instructions, the imaginary parts of the a
+// first: near unit matrices they are small, and so are the roundings while the sum has not reached its size.  Relative
+// error of an FP32 hop on links of width 0.3 against extended precision 7.26e-8; 7.60e-8 with the products added one
+// by one (16 instructions for three), 7.99e-8 as a chain that takes the products in turn.
+template <typename R> WHMC_DEV cplx<R> cdot2(cplx<R> a0, cplx<R> b0, cplx<R> a1, cplx<R> b1) {
+  return {fma(a1.re, b1.re, fma(a0.re, b0.re, fma(-a1.im, b1.im, -(a0.im * b0.im)))),
+          fma(a1.re, b1.im, fma(a0.re, b0.im, fma(a1.im, b1.re, a0.im * b0.re)))};
 }
-template <bool FUSED, typename R> WHMC_DEV cplx<R> cmsub(cplx<R> a, cplx<R> b, cplx<R> s) {
-  if (!FUSED) return s - cmul(a, b);
-  return {fma(a.im, b.im, fma(-a.re, b.re, s.re)), fma(-a.im, b.re, fma(-a.re, b.im, s.im))};
-}
-template <typename R> WHMC_DEV cplx<R> cjmad(cplx<R> a, cplx<R> b, cplx<R> s) {
-  return {fma(a.im, b.im, fma(a.re, b.re, s.re)), fma(-a.im, b.re, fma(a.re, b.im, s.im))};
-}
-// a0 b0 + a1 b1 + a2 b2: the real products of each sign as a chain of multiply-adds, the two joined at the end:
-// 14 instructions, and fewer roundings at the size of the sum than three products added up (16) or one chain of
-// all (12).  Relative error of a hop on links of width 0.3: FP32 7.64e-8, 7.94e-8 and 7.99e-8.
 template <typename R>
 WHMC_DEV cplx<R> cdot3(cplx<R> a0, cplx<R> b0, cplx<R> a1, cplx<R> b1, cplx<R> a2, cplx<R> b2) {
-  return {fma(a2.re, b2.re, fma(a1.re, b1.re, a0.re * b0.re)) - fma(a2.im, b2.im, fma(a1.im, b1.im, a0.im * b0.im)),
-          fma(a2.re, b2.im, fma(a1.re, b1.im, a0.re * b0.im)) + fma(a2.im, b2.re, fma(a1.im, b1.re, a0.im * b0.re))};
+  return {fma(a2.re, b2.re, fma(a1.re, b1.re, fma(a0.re, b0.re, fma(-a2.im, b2.im, fma(-a1.im, b1.im, -(a0.im * b0.im)))))),
+          fma(a2.re, b2.im, fma(a1.re, b1.im, fma(a0.re, b0.im, fma(a2.im, b2.re, fma(a1.im, b1.re, a0.im * b0.re)))))};
 }
 template <typename R> WHMC_DEV cplx<R> conj(cplx<R> a) { return {a.re, -a.im}; }
 template <typename R> WHMC_DEV cplx<R> times_i(cplx<R> a) { return {-a.im, a.re}; }
 template <typename R> WHMC_DEV cplx<R> times_mi(cplx<R> a) { return {a.im, -a.re}; }
-template <typename R> WHMC_DEV R norm2(cplx<R> a) { return fma(a.im, a.im, a.re * a.re); }
+template <typename R> WHMC_DEV R norm2(cplx<R> a) { return fma(a.re, a.re, a.im * a.im); }
 
 template <typename R>
 struct Spinor {
@@ -100,25 +92,19 @@ template <typename R> WHMC_DEV void zero(Spinor<R>& s) {
 }
 
 // y = U x   and   y = U^dag x   on a colour vector
-template <bool FUSED, typename R> WHMC_DEV void mul(const SU3<R>& U, const cplx<R>* x, cplx<R>* y) {
+template <typename R> WHMC_DEV void mul(const SU3<R>& U, const cplx<R>* x, cplx<R>* y) {
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    if (FUSED) y[a] = cmad<true>(U.e[a][2], x[2], cmad<true>(U.e[a][1], x[1], cmul(U.e[a][0], x[0])));
-    else y[a] = cdot3(U.e[a][0], x[0], U.e[a][1], x[1], U.e[a][2], x[2]);
-  }
+  for (int a = 0; a < 3; ++a) y[a] = cdot3(U.e[a][0], x[0], U.e[a][1], x[1], U.e[a][2], x[2]);
 }
-template <bool FUSED, typename R> WHMC_DEV void mul_dag(const SU3<R>& U, const cplx<R>* x, cplx<R>* y) {
+template <typename R> WHMC_DEV void mul_dag(const SU3<R>& U, const cplx<R>* x, cplx<R>* y) {
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    if (FUSED) y[a] = cjmad(U.e[2][a], x[2], cjmad(U.e[1][a], x[1], cjmul(U.e[0][a], x[0])));
-    else y[a] = cdot3(conj(U.e[0][a]), x[0], conj(U.e[1][a]), x[1], conj(U.e[2][a]), x[2]);
-  }
+  for (int a = 0; a < 3; ++a) y[a] = cdot3(conj(U.e[0][a]), x[0], conj(U.e[1][a]), x[1], conj(U.e[2][a]), x[2]);
 }
 // third row of an SU(3) matrix from the first two: r2 = conj(r0 x r1)
-template <bool FUSED = false, typename R> WHMC_DEV void reconstruct_row2(SU3<R>& U) {
-  U.e[2][0] = conj(cmsub<FUSED>(U.e[0][2], U.e[1][1], cmul(U.e[0][1], U.e[1][2])));
-  U.e[2][1] = conj(cmsub<FUSED>(U.e[0][0], U.e[1][2], cmul(U.e[0][2], U.e[1][0])));
-  U.e[2][2] = conj(cmsub<FUSED>(U.e[0][1], U.e[1][0], cmul(U.e[0][0], U.e[1][1])));
+template <typename R> WHMC_DEV void reconstruct_row2(SU3<R>& U) {
+  U.e[2][0] = conj(cdot2(U.e[0][1], U.e[1][2], -U.e[0][2], U.e[1][1]));
+  U.e[2][1] = conj(cdot2(U.e[0][2], U.e[1][0], -U.e[0][0], U.e[1][2]));
+  U.e[2][2] = conj(cdot2(U.e[0][0], U.e[1][1], -U.e[0][1], U.e[1][0]));
 }
 
 // 8 real parameters per link, the form of Clark, Babich, Barros, Brower and Rebbi (Comput. Phys.
@@ -179,7 +165,7 @@ WHMC_DEV double rsq(double x) { return sqrt(x); }
 WHMC_DEV float rsq(float x) { return sqrtf(x); }
 
 // U.e[0][1], U.e[0][2] set; s = U10 (t_s < 4: phase of U20) or U20 (t_s = phase of U10 + 8)
-template <bool FUSED = false, typename R> WHMC_DEV void reconstruct8(SU3<R>& U, cplx<R> s, R t00, R t_s) {
+template <typename R> WHMC_DEV void reconstruct8(SU3<R>& U, cplx<R> s, R t00, R t_s) {
   const cplx<R> a2 = U.e[0][1], a3 = U.e[0][2];
   const R n = norm2(a2) + norm2(a3);
   const bool swapped = t_s > R(4);
@@ -194,10 +180,10 @@ template <bool FUSED = false, typename R> WHMC_DEV void reconstruct8(SU3<R>& U, 
   U.e[0][0] = a1;
   U.e[1][0] = b1;
   U.e[2][0] = c1;
-  U.e[1][1] = -inv * cmad<FUSED>(ca3, cc1, cmul(cmul(ca1, a2), b1));
-  U.e[1][2] = inv * cmsub<FUSED>(cmul(ca1, a3), b1, cmul(ca2, cc1));
-  U.e[2][1] = -inv * cmsub<FUSED>(ca3, cb1, cmul(cmul(ca1, a2), c1));
-  U.e[2][2] = -inv * cmad<FUSED>(ca2, cb1, cmul(cmul(ca1, a3), c1));
+  U.e[1][1] = -inv * cdot2(cmul(ca1, a2), b1, ca3, cc1);
+  U.e[1][2] = inv * cdot2(ca2, cc1, -cmul(ca1, a3), b1);
+  U.e[2][1] = -inv * cdot2(cmul(ca1, a2), c1, -ca3, cb1);
+  U.e[2][2] = -inv * cdot2(cmul(ca1, a3), c1, ca2, cb1);
 }
 
 // ------------------------------------------------------------------ geometry
@@ -607,7 +593,7 @@ struct LinkF16_12T {
       U.e[(2 * k) / 3][(2 * k) % 3] = {h2f((unsigned short)(v.x & 0xffffu)), h2f((unsigned short)(v.x >> 16))};
       U.e[(2 * k + 1) / 3][(2 * k + 1) % 3] = {h2f((unsigned short)(v.y & 0xffffu)), h2f((unsigned short)(v.y >> 16))};
     }
-    reconstruct_row2<true>(U);
+    reconstruct_row2(U);
   }
 };
 
@@ -655,7 +641,7 @@ struct LinkF16_8T {
     U.e[0][2] = {h2f((unsigned short)(w.y & 0xffffu)), h2f((unsigned short)(w.y >> 16))};
     const cplx<float> b1 = {h2f((unsigned short)(w.z & 0xffffu)), h2f((unsigned short)(w.z >> 16))};
     const float pi = 3.14159265358979f;
-    reconstruct8<true>(U, b1, pi * h2f((unsigned short)(w.w & 0xffffu)), pi * h2f((unsigned short)(w.w >> 16)));
+    reconstruct8(U, b1, pi * h2f((unsigned short)(w.w & 0xffffu)), pi * h2f((unsigned short)(w.w >> 16)));
   }
 };
 
