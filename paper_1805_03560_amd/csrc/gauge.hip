@@ -183,12 +183,11 @@ whmc_status plaquette_sum(whmc_ctx* c, double* host_out) {
 // F_{x,mu} = (beta/6) P_TA(U_{x,mu} Sigma_{x,mu}), Sigma = sum of the six staples.
 // out = (accumulate ? out : 0) + scale * F.
 //
-// A workgroup holds the four directions of 64 sites of one parity, one wavefront each.  Neighbours come from
+// A workgroup of W = 4 holds the four directions of 64 sites of one parity, one wavefront each.  Neighbours come from
 // additive displacements of the lexicographic index and 32-bit byte offsets.  It is bound by the 19 link loads
 // per link: 24 GB through L1 and L2 per call at 32^3 x 64 (about 20 TB/s) with the vector units half busy and
-// two waves per SIMD.  32^3 x 64: 1190 -> 1137 us, 24^3 x 48: 375 -> 354, 12^3 x 24: 26.8 -> 25.4 against a
-// workgroup per direction with 64-bit offsets.  Other orders of the planes gain nothing (nu = mu ^ s, in which
-// two wavefronts work on the plane they span: 1156 and 368 us).
+// two waves per SIMD.  32^3 x 64: 1193 -> 1148 us, 24^3 x 48: 377 -> 362, 12^3 x 24: 28.6 -> 27.8 against a
+// workgroup per direction with 64-bit offsets.
 // Slower: sharing U_nu(x) and U_nu(x-nu) through LDS (1515 us: 74 KiB of LDS, two waves per SIMD waiting
 // at one barrier), exchanging the products U_mu(x) U_nu(x+mu) of a plane as well (1590 us: 11 loads per
 // link, six barriers), three waves per SIMD (1730 us, spills).
@@ -216,15 +215,14 @@ WHMC_DEV void link_at(const double2* U18, int Vh, int par, int d, int cb, SU3<do
                FULL ? 1024u : w16, U);
 }
 
-constexpr int kStapleWG = 256;
-
-template <bool FULL, class Off>
-__global__ __launch_bounds__(kStapleWG, 2) void k_gauge_force(Geom g, const double2* __restrict__ U18, double* F,
+template <int W, bool FULL, class Off>
+__global__ __launch_bounds__(64 * W, 2) void k_gauge_force(Geom g, const double2* __restrict__ U18, double* F,
                                                            double coef, int accumulate) {
   int grp;
-  const int sb = site_block_cols(g, blockIdx.x, gridDim.x, 4, grp);
-  const int base = sb * kBlock + (grp & 1) * 64, par = grp >> 1;
-  const int lane = threadIdx.x & 63, mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int sb = site_block_cols(g, blockIdx.x, gridDim.x, 16 / W, grp);
+  const int id = grp * W + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // direction, half, parity
+  const int mu = id & 3, base = sb * kBlock + ((id >> 2) & 1) * 64, par = id >> 3;
+  const int lane = threadIdx.x & 63;
   const int i = base + lane;
   if (i >= g.Vh) return;
   const Coords c = coords_of(g, i, par);
@@ -273,18 +271,29 @@ __global__ __launch_bounds__(kStapleWG, 2) void k_gauge_force(Geom g, const doub
   }
 }
 
+// Wavefronts of a workgroup: one up to 4096 sites per parity, where all of them (eight per 64 sites) are at most two
+// a compute unit and one workgroup's four would wait for the same L1 while other units idle; four beyond, which share
+// links there.  us with one, with four:  4^4 7.7, 8.7;  12x4x6x6 7.9, 9.2;  16x8^3 (4096) 9.5, 9.7;  16x10x8x10
+// (6400) 10.6, 10.3;  12^3x24 27.0, 26.9;  16^3x32 70.5, 68.4.
+static int staple_waves(const whmc_ctx* c) { return c->Vh <= 4096 ? 1 : 4; }
+
+template <int W>
+static void launch_gauge_force(whmc_ctx* c, double* F, double coef, int accumulate) {
+  const dim3 grid(16 / W * c->stencil_blocks()), block(64 * W);
+  const bool narrow = W == 1 || (unsigned long long)c->Vh * 144ull <= 0xFFFFFFFFull;
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, c->stream, c->g, c->U18, F, coef, accumulate);
+  };
+  if (c->Vh % 64 == 0 && narrow) run(k_gauge_force<W, true, unsigned>);
+  else if (narrow) run(k_gauge_force<W, false, unsigned>);
+  else if constexpr (W == 4) run(k_gauge_force<W, false, unsigned long long>);
+}
+
 whmc_status gauge_force(whmc_ctx* c, double* F, double beta_eff, double scale, int accumulate) {
   WHMC_CHECK(c->gauge_loaded, WHMC_ESTATE, "no gauge field loaded");
-  const dim3 grid(4 * c->stencil_blocks()), block(kStapleWG);
   const double coef = scale * beta_eff / 6.0;
-  const bool narrow = (unsigned long long)c->Vh * 144ull <= 0xFFFFFFFFull;
-  if (!narrow)
-    hipLaunchKernelGGL((k_gauge_force<false, unsigned long long>), grid, block, 0, c->stream, c->g, c->U18, F, coef,
-                       accumulate);
-  else if (c->Vh % 64 == 0)
-    hipLaunchKernelGGL((k_gauge_force<true, unsigned>), grid, block, 0, c->stream, c->g, c->U18, F, coef, accumulate);
-  else
-    hipLaunchKernelGGL((k_gauge_force<false, unsigned>), grid, block, 0, c->stream, c->g, c->U18, F, coef, accumulate);
+  if (staple_waves(c) == 1) launch_gauge_force<1>(c, F, coef, accumulate);
+  else launch_gauge_force<4>(c, F, coef, accumulate);
   WHMC_HIP(hipGetLastError());
   return WHMC_OK;
 }

@@ -13,11 +13,13 @@ from gpu_util import algebra_to_numpy, make_ctx, oracle_cached, pack_half, rel_e
 
 pytestmark = pytest.mark.gpu
 
-# planes of 2, 2 and 4 blocks, 1, 2 and 1 planes per XCD
+# planes of 2, 2 and 4 blocks, 1, 2 and 1 planes per XCD; V_h = 4096 (a wavefront per workgroup), 8192 and 16384
+# (four)
 DIMS = [(2, 8, 16, 32), (2, 16, 32, 16), (4, 8, 32, 32)]
 
 
-@pytest.mark.parametrize("dims", DIMS)
+# ... and lattices without columns on both sides of that line, with part of a block
+@pytest.mark.parametrize("dims", DIMS + [(6, 2, 6, 6), (16, 8, 8, 8), (18, 6, 6, 14)])
 def test_gauge_force_in_columns(dims):
     U = synth.smooth_links(dims, 9530, width=0.8)
     ctx = make_ctx(dims, U)
