@@ -339,7 +339,7 @@ static whmc_status enqueue_iters(whmc_ctx* c, const Lnk& L, S p, S t, S u, S v, 
 template <class Lnk>
 static whmc_status cg_f64(whmc_ctx* c, double* x, const double* b, double kappa, const whmc_cg_params* prm,
                           whmc_cg_stats* st, Lnk L, int links) {
-  const bool split = split_hops(c, WHMC_F64, links, 1);
+  const bool split = split_solves(c, WHMC_F64, links);
   const double k2 = kappa * kappa;
   Timer tm;
   const size_t hb = (size_t)c->Vh * 192;
@@ -417,7 +417,7 @@ template <class Lnk, class S, class SR>
 static whmc_status cg_mixed(whmc_ctx* c, double* x, const double* b, double kappa, const whmc_cg_params* prm,
                             whmc_cg_stats* st, Lnk L, int sprec, S (*mk)(void*, int), SR (*mkr)(void*, int),
                             int rprec) {
-  const bool split = split_hops(c, sprec, prm->links, 1);
+  const bool split = split_solves(c, sprec, prm->links);
   const double k2 = kappa * kappa;
   Timer tm;
   const int Vh = c->Vh;

@@ -175,7 +175,8 @@ whmc_status hop(whmc_ctx* c, int prec, int links, int par, int dag, void* out, c
 
 // ---- direction-split kernels for small lattices (split.hip)
 bool split_fits(const whmc_ctx* c, int prec, int links, int nrhs);   // whether they beat a thread per site
-bool split_hops(const whmc_ctx* c, int prec, int links, int nrhs);   // whether a hop, M^dag M or CG takes them
+bool split_hops(const whmc_ctx* c, int prec, int links, int nrhs);   // whether a hop, M^dag M or multi-RHS CG takes them
+bool split_solves(const whmc_ctx* c, int prec, int links);           // ... or a CG on one right-hand side
 whmc_status split_hop(whmc_ctx* c, int prec, int links, int par, int dag, int nrhs, void* out, const void* in,
                       const void* x, double a, const double* b);   // b[nrhs]
 // out_r = M(kappa_r)^(dag) in_r on nrhs <= kMaxRhs full spinors, FP64 with 18-real links

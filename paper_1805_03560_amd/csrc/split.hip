@@ -389,6 +389,16 @@ bool split_hops(const whmc_ctx* c, int prec, int links, int nrhs) {
   return !sweep_rhs(c, prec, links, nrhs) || (prec == WHMC_F64 && nrhs == 2);
 }
 
+// ... and of single right-hand sides' CG solves.  Where time slices are whole blocks the other kernels have their
+// schedule and an XCD its part of every slice; up to this size these are ahead of it all the same.  Where they are not,
+// the line is lower for 12- and 18-real links, us per iteration with one thread per site and so: 30x20x18x20
+// (108 000) FP64-12 137.0, 134.9, FP32-12 79.4, 77.9;  32x20x20x18 (115 200) FP64-18 165.4, 167.1, FP64-12 141.2,
+// 146.3, FP32-12 80.7, 82.1, FP64-8 134.3, 131.1;  whole slices, 36x16x20x20 (115 200) FP64-18 180.3, 162.7, FP64-12
+// 156.0, 143.2, FP32-12 91.3, 80.6.
+bool split_solves(const whmc_ctx* c, int prec, int links) {
+  return split_hops(c, prec, links, 1) && (c->g.nbs > 0 || links == WHMC_L8 || c->Vh <= 110592);
+}
+
 template <int DAG, int MODE, class Lnk, class S, class SR>
 static void launch_split(whmc_ctx* c, int par, int nrhs, const Lnk& L, S in, S x, S out, S p, SR r, SR xs, double a,
                          const SplitK2& k2, unsigned mask, CGScalars* sc, const double* part_in,
