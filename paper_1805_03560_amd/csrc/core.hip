@@ -838,7 +838,7 @@ whmc_status whmc_apply_Moo(whmc_ctx* c, double* out, const double* in, double ka
 // each, four 227; 16^3 x 32, one 70, two 52 each, four 41, six 38).
 static int mdagm_batch(const whmc_ctx* c, int nrhs, int eo) {
   nrhs = std::min(nrhs, kMaxRhs);
-  if (eo && !c->split_off && !split_hops(c, WHMC_F64, WHMC_L18, nrhs) && sweep_rhs(c, WHMC_F64, WHMC_L18, nrhs))
+  if (eo && !split_hops(c, WHMC_F64, WHMC_L18, nrhs) && sweep_rhs(c, WHMC_F64, WHMC_L18, nrhs))
     return std::min(nrhs, std::max(4, 524288 / c->Vh));
   for (int n = nrhs; n > 1; --n)
     if (eo ? split_hops(c, WHMC_F64, WHMC_L18, n) : split_fits(c, WHMC_F64, WHMC_L18, 2 * n)) return n;

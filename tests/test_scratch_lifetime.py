@@ -101,14 +101,33 @@ print("ok")
 """
 
 
-# the direction-split kernels (eo = 1 and 0), the sweep kernels and the largest lattices' batches of four
-@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (16, 16, 16, 16), (48, 24, 24, 24)])
-@pytest.mark.parametrize("counts", [(1, 3, 16, 2), (3, 9), (1, 2, 4, 8, 16, 1), (20, 1)])
-def test_no_scratch_of_an_earlier_call_is_freed(tmp_path, dims, counts):
+def _run(tmp_path, driver, dims, counts):
     src = tmp_path / "stub.c"
     src.write_text(STUB)
     stub = str(tmp_path / "stub.so")
     subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-w", str(src), "-o", stub], check=True)
-    r = subprocess.run([sys.executable, "-c", DRIVER, stub, LIB, ",".join(map(str, dims)), ",".join(map(str, counts))],
+    r = subprocess.run([sys.executable, "-c", driver, stub, LIB, ",".join(map(str, dims)), ",".join(map(str, counts))],
                        capture_output=True, text=True)
     assert r.returncode == 0 and r.stdout.strip() == "ok", r.stderr[-2000:]
+
+
+DRIVER_BATCH = DRIVER[:DRIVER.index("for eo in")] + r"""
+L.whmc_set_option.argtypes = [P, ctypes.c_int, ctypes.c_longlong]
+ok(L.whmc_set_option(ctx, 2, 0))    # WHMC_OPT_HOP_SCHEDULE
+used = stub.stub_used()
+ok(call(4, 1))
+assert stub.stub_used() - used == 4 * per
+print("ok")
+"""
+
+
+# the direction-split kernels (eo = 1 and 0), the sweep kernels and the largest lattices' batches of four
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (16, 16, 16, 16), (48, 24, 24, 24)])
+@pytest.mark.parametrize("counts", [(1, 3, 16, 2), (3, 9), (1, 2, 4, 8, 16, 1), (20, 1)])
+def test_no_scratch_of_an_earlier_call_is_freed(tmp_path, dims, counts):
+    _run(tmp_path, DRIVER, dims, counts)
+
+
+def test_several_masses_share_a_pass_whatever_the_schedule(tmp_path):
+    """large lattices: an explicit schedule of the single-RHS kernels does not take the batches away"""
+    _run(tmp_path, DRIVER_BATCH, (48, 24, 24, 24), (4,))
