@@ -113,14 +113,19 @@ whmc_status whmc_set_stream(whmc_ctx* ctx, void* stream);
  *                              of their XCD.  FP32 / FP16 kernels and 8-real links are never capped.
  *                              EARG if the device's LDS limits do not allow the value.  Results do
  *                              not depend on it.
- * Small lattices take stencil and CG kernels that spread a site's eight directions over a workgroup and
- * have no such schedule; setting WHMC_OPT_HOP_SCHEDULE or WHMC_OPT_HOP_WG_PER_CU selects the kernels with
- * one thread per site there too (a hop's bits are the same). */
+ *   WHMC_OPT_HOP_KERNEL        which single-RHS stencil and CG kernels small lattices take: 0 = the library's choice
+ *                              (default), kernels that spread a site's eight directions over a workgroup, which
+ *                              have no schedule or cap; 1 = one thread per site, as on larger lattices.  Setting
+ *                              WHMC_OPT_HOP_SCHEDULE or WHMC_OPT_HOP_WG_PER_CU, to whichever value, selects 1;
+ *                              a program that stores and restores options sets this one last.  Several
+ *                              right-hand sides without a blocking follow it on small lattices only.  A hop's
+ *                              bits do not depend on it. */
 #define WHMC_OPT_HOP_SCHEDULE 2
 #define WHMC_OPT_HOP_CHUNK 3
 #define WHMC_OPT_FORCE_KERNEL 4
 #define WHMC_OPT_FORCE_CHUNK 5
 #define WHMC_OPT_HOP_WG_PER_CU 6
+#define WHMC_OPT_HOP_KERNEL 7
 whmc_status whmc_set_option(whmc_ctx* ctx, int option, long long value);
 whmc_status whmc_get_option(const whmc_ctx* ctx, int option, long long* value);
 

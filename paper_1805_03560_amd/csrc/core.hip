@@ -1058,6 +1058,10 @@ whmc_status whmc_set_option(whmc_ctx* c, int option, long long value) {
                  "128-site blocks");
       c->split_off = true;
       return WHMC_OK;
+    case WHMC_OPT_HOP_KERNEL:
+      WHMC_CHECK(value == 0 || value == 1, WHMC_EARG, "whmc_set_option: the hop kernel must be 0 or 1");
+      c->split_off = value == 1;
+      return WHMC_OK;
     default:
       set_error("whmc_set_option: unknown option " + std::to_string(option));
       return WHMC_EARG;
@@ -1071,6 +1075,7 @@ whmc_status whmc_get_option(const whmc_ctx* c, int option, long long* value) {
     case WHMC_OPT_HOP_SCHEDULE: *value = c->g.sched; return WHMC_OK;
     case WHMC_OPT_HOP_WG_PER_CU: *value = c->hop_wg_per_cu; return WHMC_OK;
     case WHMC_OPT_HOP_CHUNK: *value = c->hop_chunk; return WHMC_OK;
+    case WHMC_OPT_HOP_KERNEL: *value = c->split_off ? 1 : 0; return WHMC_OK;
     case WHMC_OPT_FORCE_KERNEL: *value = c->force_kernel; return WHMC_OK;
     case WHMC_OPT_FORCE_CHUNK: *value = c->force_chunk; return WHMC_OK;
     default:

@@ -116,7 +116,7 @@ struct whmc_ctx {
   // reserves stencil_lds bytes of LDS it does not use, so that at most hop_wg_per_cu workgroups fit
   // on a compute unit (0 = no cap, stencil_lds = 0).  Fewer sites in flight per XCD keep the
   // neighbour spinors of the sites in flight inside that XCD's L2.
-  bool split_off = false;        // a schedule or cap was asked for: no direction-split kernels
+  bool split_off = false;        // no direction-split kernels (WHMC_OPT_HOP_KERNEL = 1)
   int hop_wg_per_cu = 0;
   unsigned stencil_lds = 0;
   int lds_per_cu = 0, lds_per_wg = 0;   // device limits, read at creation
