@@ -373,7 +373,8 @@ class Context:
         return out
 
     def autotune(self, prec, links, nrhs):
-        """-> (rhs_block, rhs_lanes, rhs_order, microseconds per launch) of the fastest multi-RHS blocking"""
+        """-> (rhs_block, rhs_lanes, rhs_order, microseconds per launch) of the fastest multi-RHS blocking; calls with
+        rhs_block = rhs_lanes = 0 use it where they have no faster kernels without one"""
         nb, lanes, order, us = ctypes.c_int(), ctypes.c_int(), ctypes.c_int(), ctypes.c_double()
         _check(lib().whmc_autotune(self._h, prec, links, nrhs, ctypes.byref(nb), ctypes.byref(lanes),
                                    ctypes.byref(order), ctypes.byref(us)))
