@@ -597,7 +597,7 @@ static whmc_status resolve_blocking(whmc_ctx* c, int prec, int links, int nrhs, 
 }
 
 // the formats of the multi-RHS kernels
-static bool split_format(int prec, int links) {
+static bool multi_format(int prec, int links) {
   if (links != WHMC_L18 && links != WHMC_L12 && links != WHMC_L8) return false;
   return prec == WHMC_F64 || ((prec == WHMC_F32 || prec == WHMC_F16) && links != WHMC_L18);
 }
@@ -773,6 +773,8 @@ static whmc_status residual_multi(whmc_ctx* c, unsigned mask, int nrhs, const do
     WHMC_HIP(hipGetLastError());
     return WHMC_OK;
   }
+  // left are lattices below 32768 sites per parity that don't take the direction-split kernels (streamed links, or
+  // WHMC_OPT_HOP_KERNEL = 1), and fields beyond 4 GiB
   Blocking bk;
   WHMC_TRY(autotune_blocking(c, WHMC_F64, WHMC_L18, nrhs, &bk, nullptr));
   const int Vh = c->Vh;
@@ -1010,12 +1012,12 @@ extern "C" whmc_status whmc_apply_H_multi(whmc_ctx* c, void* out, const void* in
   WHMC_CHECK(c && out && in && out != in, WHMC_EARG, "whmc_apply_H_multi: bad pointers");
   WHMC_CHECK(out_parity == 0 || out_parity == 1, WHMC_EARG, "whmc_apply_H_multi: out_parity must be 0 or 1");
   WHMC_CHECK(nrhs >= 1 && nrhs <= kMaxRhs, WHMC_EARG, "whmc_apply_H_multi: nrhs must be in [1, 16]");
-  if (rhs_block <= 0 && rhs_lanes <= 0 && split_format(prec, links) && split_hops(c, prec, links, nrhs)) {
+  if (rhs_block <= 0 && rhs_lanes <= 0 && multi_format(prec, links) && split_hops(c, prec, links, nrhs)) {
     double ones[kMaxRhs];
     for (double& v : ones) v = 1.0;
     return split_hop(c, prec, links, out_parity, dagger ? 1 : 0, nrhs, out, in, nullptr, 0.0, ones);
   }
-  if (rhs_block <= 0 && rhs_lanes <= 0 && split_format(prec, links) && sweep_rhs(c, prec, links, nrhs))
+  if (rhs_block <= 0 && rhs_lanes <= 0 && multi_format(prec, links) && sweep_rhs(c, prec, links, nrhs))
     return sweep_hop(c, prec, links, out_parity, dagger ? 1 : 0, nrhs, out, in, ~0u, nullptr);
   Blocking b;
   WHMC_TRY(resolve_blocking(c, prec, links, nrhs, rhs_block, rhs_lanes, rhs_order, &b));

@@ -13,7 +13,7 @@ constexpr int kSplitSites = 64, kSplitWG = 512;
 
 // ------------------------------------------------------------------ addresses
 // A site of a field as a byte offset from the field's (uniform) base and the distance of its entries, both
-// 32 bits: the half fields these kernels are used on stay below 4 GiB (narrow_fields).
+// 32 bits: the half fields these kernels are used on stay below 4 GiB (split_fits, sweep_rhs).
 struct At {
   unsigned off, w;
   int i;
@@ -196,5 +196,12 @@ WHMC_DEV void hop_apply_d(int d, const SU3<R>& U, const Spinor<R>& s, R sc, bool
 struct SplitK2 {
   double v[kMaxRhs];
 };
+
+// ------------------------------------------------------------------ fields from pointers
+inline SpinorF64 f64(const void* p, int Vh) { return SpinorF64{(double2*)p, Vh}; }
+inline SpinorF32 f32(const void* p, int Vh) { return SpinorF32{(float4*)p, Vh}; }
+inline SpinorF16 f16(const void* p, int Vh) {
+  return SpinorF16{(uint4*)p, p ? (float*)((uint4*)p + (size_t)3 * Vh) : nullptr, Vh};
+}
 
 }  // namespace whmc

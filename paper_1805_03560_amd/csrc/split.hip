@@ -337,12 +337,6 @@ __global__ __launch_bounds__(kSplitWG, 4) void k_split_ph(FastDiv by_nrhs, int n
 }
 
 // ------------------------------------------------------------------ host side
-static SpinorF64 f64(const void* p, int Vh) { return SpinorF64{(double2*)p, Vh}; }
-static SpinorF32 f32(const void* p, int Vh) { return SpinorF32{(float4*)p, Vh}; }
-static SpinorF16 f16(const void* p, int Vh) {
-  return SpinorF16{(uint4*)p, p ? (float*)((uint4*)p + (size_t)3 * Vh) : nullptr, Vh};
-}
-
 // f(link accessor, spinor maker) for a format; the links are cached, never streamed, on these lattices
 template <class F>
 static whmc_status with_links(whmc_ctx* c, int prec, int links, F&& f) {

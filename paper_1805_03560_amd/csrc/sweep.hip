@@ -115,9 +115,6 @@ __global__ __launch_bounds__(kSplitWG, 4) void k_sweep(Geom g, int par, int nrhs
 }
 
 // ------------------------------------------------------------------ host side
-static SpinorF64 f64(const void* p, int Vh) { return SpinorF64{(double2*)p, Vh}; }
-static SpinorF32 f32(const void* p, int Vh) { return SpinorF32{(float4*)p, Vh}; }
-
 template <bool NT, class F>
 static void with_links_nt(whmc_ctx* c, int prec, int links, F&& f) {
   const int Vh = c->Vh;
