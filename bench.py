@@ -153,9 +153,9 @@ def profile_kernel(name, whmc, torch, np):
     """a few launches of one kernel on its benchmark workload, for counter passes:
     hop_f16_l12: the chained FP16 even/odd pair (12-real links) on 32^3 x 64;
     hop_formats: the chained pair in every storage format on 32^3 x 64 (3 timed steps each);
-    mhop_f64_12rhs / mhop_f16_12rhs: the multi-RHS hop for 12 right-hand sides on 24^3 x 48 by the
-    library's choice (the autotuned blocking in FP16); pf_force_24: the pair force of 24 (X, Y) pairs
-    (kappa^4 filter, n_t = 23) on 32^3 x 64."""
+    mhop_f64_12rhs / mhop_f16_12rhs: the multi-RHS hop for 12 right-hand sides on 24^3 x 48 with the
+    autotuned blocking; pf_force_24: the pair force of 24 (X, Y) pairs (kappa^4 filter, n_t = 23)
+    on 32^3 x 64."""
     from paper_1805_03560_amd import synth
     dev = torch.device("cuda", 0)
     if name.startswith("mhop"):
@@ -192,7 +192,7 @@ def profile_kernel(name, whmc, torch, np):
         nb, lanes, order, _ = ctx.autotune(prec, links, n)
         o = ctx.half_spinor(prec, n)
         for _ in range(3):
-            ctx.apply_H_multi(bp, 0, n, prec=prec, links=links, out=o)
+            ctx.apply_H_multi(bp, 0, n, prec=prec, links=links, rhs_block=nb, rhs_lanes=lanes, rhs_order=order, out=o)
         info = {"blocking": [nb, lanes, order]}
     else:
         phi = ctx.pack_spinor(torch.from_numpy(synth.gaussian_spinor(Vh, 3003)).to(dev), 0)

@@ -186,8 +186,8 @@ whmc_status plaquette_sum(whmc_ctx* c, double* host_out) {
 // A workgroup of W = 4 holds the four directions of 64 sites of one parity, one wavefront each.  Neighbours come from
 // additive displacements of the lexicographic index and 32-bit byte offsets.  It is bound by the 19 link loads
 // per link: 24 GB through L1 and L2 per call at 32^3 x 64 (about 20 TB/s) with the vector units half busy and
-// two waves per SIMD.  32^3 x 64: 1193 -> 1148 us, 24^3 x 48: 377 -> 362, 12^3 x 24: 28.6 -> 27.8 against a
-// workgroup per direction with 64-bit offsets.
+// two waves per SIMD.  32^3 x 64: 1193 -> 1148 us back to back, 1287 -> 1241 between link updates, 24^3 x 48:
+// 377 -> 362, 12^3 x 24: 28.6 -> 27.8 against a workgroup per direction with 64-bit offsets.
 // Slower: sharing U_nu(x) and U_nu(x-nu) through LDS (1515 us: 74 KiB of LDS, two waves per SIMD waiting
 // at one barrier), exchanging the products U_mu(x) U_nu(x+mu) of a plane as well (1590 us: 11 loads per
 // link, six barriers), three waves per SIMD (1730 us, spills).

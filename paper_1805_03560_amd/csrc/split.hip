@@ -366,8 +366,8 @@ static int split_blocks(const whmc_ctx* c) { return (c->Vh + kSplitSites - 1) / 
 // 16^3x20x40 two rhs FP32 147 -> 126; beyond the lines: 16^3x32 two rhs FP16 81 -> 84, 12-rhs hops at
 // 16^3x32 FP64 129 -> 139 and FP16 39 -> 53, 20^3x40 one rhs FP64 250 -> 271.  FP16 has the least work
 // per site, so its line lies at a total of output sites; FP64 and FP32 have one for the lattice and FP64
-// one for the total.  A schedule or cap that the caller sets selects the one-thread-per-site kernels,
-// which it is about, and so do streamed links.
+// one for the total.  WHMC_OPT_HOP_KERNEL = 1, which a schedule or cap that the caller sets brings with it, selects
+// the one-thread-per-site kernels, and so do streamed links.
 bool split_fits(const whmc_ctx* c, int prec, int links, int nrhs) {
   if (c->split_off || c->stream_links(prec, links)) return false;
   const long long total = (long long)c->Vh * nrhs;
