@@ -29,7 +29,7 @@ namespace whmc {
 WHMC_DEV bool halted(const CGScalars* sc) { return sc->done | sc->pause; }
 
 template <class Lnk, class S>
-__global__ __launch_bounds__(kBlock) void k_cg1(Geom g, Lnk L, S p, S t, const CGScalars* sc) {
+__global__ __launch_bounds__(kBlock) WHMC_WAVES(Lnk) void k_cg1(Geom g, Lnk L, S p, S t, const CGScalars* sc) {
   if (halted(sc)) return;
   using R = typename S::Real;
   const int i = site_block(g, blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
@@ -40,7 +40,7 @@ __global__ __launch_bounds__(kBlock) void k_cg1(Geom g, Lnk L, S p, S t, const C
 }
 
 template <class Lnk, class S>
-__global__ __launch_bounds__(kBlock) void k_cg2(Geom g, Lnk L, S t, S p, S u, double k2, CGScalars* sc, Reduce red) {
+__global__ __launch_bounds__(kBlock) WHMC_WAVES(Lnk) void k_cg2(Geom g, Lnk L, S t, S p, S u, double k2, CGScalars* sc, Reduce red) {
   if (halted(sc)) return;
   using R = typename S::Real;
   const int i = site_block(g, blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(kFinWG) void k_cg2_fin(CGScalars* sc, const double*
 }
 
 template <class Lnk, class S>
-__global__ __launch_bounds__(kBlock) void k_cg3(Geom g, Lnk L, S u, S v, const CGScalars* sc) {
+__global__ __launch_bounds__(kBlock) WHMC_WAVES(Lnk) void k_cg3(Geom g, Lnk L, S u, S v, const CGScalars* sc) {
   if (halted(sc)) return;
   using R = typename S::Real;
   const int i = site_block(g, blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
@@ -85,7 +85,7 @@ __global__ __launch_bounds__(kBlock) void k_cg3(Geom g, Lnk L, S u, S v, const C
 }
 
 template <class Lnk, class S, class SR, bool MIXED>
-__global__ __launch_bounds__(kBlock) void k_cg4(Geom g, Lnk L, S v, S u, S p, SR r, SR x, double k2, CGScalars* sc,
+__global__ __launch_bounds__(kBlock) WHMC_WAVES(Lnk) void k_cg4(Geom g, Lnk L, S v, S u, S p, SR r, SR x, double k2, CGScalars* sc,
                                                 Reduce red) {
   if (halted(sc)) return;
   using R = typename S::Real;

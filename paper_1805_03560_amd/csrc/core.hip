@@ -59,7 +59,7 @@ whmc_status workspace(whmc_ctx* c, const std::string& name, size_t bytes, void**
 // out = a x + b H_{par,1-par}^{(dag)} in; NTS: non-temporal output store (apply_H on large lattices,
 // where the result is not read back by the next kernel); NORM: FP64 |out|^2 reduction.
 template <int DAG, bool XPAY, bool NORM, bool NTS, class Lnk, class SIn, class SX, class SOut>
-__global__ __launch_bounds__(kBlock) void k_hop(Geom g, int par, Lnk L, SIn in, SX x, SOut out, double a,
+__global__ __launch_bounds__(kBlock) WHMC_WAVES(Lnk) void k_hop(Geom g, int par, Lnk L, SIn in, SX x, SOut out, double a,
                                                 double b, Reduce red, double* norm_out) {
   using R = typename SOut::Real;
   const int i = site_block(g, blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
@@ -149,7 +149,7 @@ static whmc_status hop_nt(whmc_ctx* c, int prec, int links, int par, int dag, vo
 // Full-lattice H in one launch of 2 nb workgroups: each XCD applies both parity blocks of H to the
 // sites of its own region.
 template <int DAG, bool NTS, class Lnk, class S>
-__global__ __launch_bounds__(kBlock) void k_hop_full(Geom g, Lnk L, S in_e, S in_o, S out_e, S out_o) {
+__global__ __launch_bounds__(kBlock) WHMC_WAVES(Lnk) void k_hop_full(Geom g, Lnk L, S in_e, S in_o, S out_e, S out_o) {
   using R = typename S::Real;
   int par;
   const int i = site_block_pair(g, blockIdx.x, gridDim.x >> 1, par) * kBlock + threadIdx.x;

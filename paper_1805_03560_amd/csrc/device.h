@@ -56,13 +56,23 @@ template <typename R> WHMC_DEV cplx<R> axpby(R a, cplx<R> x, R b, cplx<R> y) {
 // a0 b0 + a1 b1 (+ a2 b2) as one chain of multiply-adds, eight (twelve) instructions, the imaginary parts of the a
 // first: near unit matrices they are small, and so are the roundings while the sum has not reached its size.  Relative
 // error of an FP32 hop on links of width 0.3 against extended precision 7.26e-8; 7.60e-8 with the products added one
-// by one (16 instructions for three), 7.99e-8 as a chain that takes the products in turn.
-template <typename R> WHMC_DEV cplx<R> cdot2(cplx<R> a0, cplx<R> b0, cplx<R> a1, cplx<R> b1) {
+// by one (16 instructions for three), 7.99e-8 as a chain that takes the products in turn.  IN_TURN: that chain, for
+// fields and links stored in half precision, whose own rounding (3e-4) hides the difference; there it is faster
+// (24^3 x 48 FP16: 12 rhs by blocks 205 us a hop against 230, one rhs 24.1 against 26.3).
+template <bool IN_TURN = false, typename R>
+WHMC_DEV cplx<R> cdot2(cplx<R> a0, cplx<R> b0, cplx<R> a1, cplx<R> b1) {
+  if (IN_TURN)
+    return {fma(-a1.im, b1.im, fma(a1.re, b1.re, fma(-a0.im, b0.im, a0.re * b0.re))),
+            fma(a1.im, b1.re, fma(a1.re, b1.im, fma(a0.im, b0.re, a0.re * b0.im)))};
   return {fma(a1.re, b1.re, fma(a0.re, b0.re, fma(-a1.im, b1.im, -(a0.im * b0.im)))),
           fma(a1.re, b1.im, fma(a0.re, b0.im, fma(a1.im, b1.re, a0.im * b0.re)))};
 }
-template <typename R>
+template <bool IN_TURN, typename R>
 WHMC_DEV cplx<R> cdot3(cplx<R> a0, cplx<R> b0, cplx<R> a1, cplx<R> b1, cplx<R> a2, cplx<R> b2) {
+  if (IN_TURN) {
+    const cplx<R> s = cdot2<true>(a0, b0, a1, b1);
+    return {fma(-a2.im, b2.im, fma(a2.re, b2.re, s.re)), fma(a2.im, b2.re, fma(a2.re, b2.im, s.im))};
+  }
   return {fma(a2.re, b2.re, fma(a1.re, b1.re, fma(a0.re, b0.re, fma(-a2.im, b2.im, fma(-a1.im, b1.im, -(a0.im * b0.im)))))),
           fma(a2.re, b2.im, fma(a1.re, b1.im, fma(a0.re, b0.im, fma(a2.im, b2.re, fma(a1.im, b1.re, a0.im * b0.re)))))};
 }
@@ -92,19 +102,20 @@ template <typename R> WHMC_DEV void zero(Spinor<R>& s) {
 }
 
 // y = U x   and   y = U^dag x   on a colour vector
-template <typename R> WHMC_DEV void mul(const SU3<R>& U, const cplx<R>* x, cplx<R>* y) {
+template <bool IN_TURN, typename R> WHMC_DEV void mul(const SU3<R>& U, const cplx<R>* x, cplx<R>* y) {
 #pragma unroll
-  for (int a = 0; a < 3; ++a) y[a] = cdot3(U.e[a][0], x[0], U.e[a][1], x[1], U.e[a][2], x[2]);
+  for (int a = 0; a < 3; ++a) y[a] = cdot3<IN_TURN>(U.e[a][0], x[0], U.e[a][1], x[1], U.e[a][2], x[2]);
 }
-template <typename R> WHMC_DEV void mul_dag(const SU3<R>& U, const cplx<R>* x, cplx<R>* y) {
+template <bool IN_TURN, typename R> WHMC_DEV void mul_dag(const SU3<R>& U, const cplx<R>* x, cplx<R>* y) {
 #pragma unroll
-  for (int a = 0; a < 3; ++a) y[a] = cdot3(conj(U.e[0][a]), x[0], conj(U.e[1][a]), x[1], conj(U.e[2][a]), x[2]);
+  for (int a = 0; a < 3; ++a)
+    y[a] = cdot3<IN_TURN>(conj(U.e[0][a]), x[0], conj(U.e[1][a]), x[1], conj(U.e[2][a]), x[2]);
 }
 // third row of an SU(3) matrix from the first two: r2 = conj(r0 x r1)
-template <typename R> WHMC_DEV void reconstruct_row2(SU3<R>& U) {
-  U.e[2][0] = conj(cdot2(U.e[0][1], U.e[1][2], -U.e[0][2], U.e[1][1]));
-  U.e[2][1] = conj(cdot2(U.e[0][2], U.e[1][0], -U.e[0][0], U.e[1][2]));
-  U.e[2][2] = conj(cdot2(U.e[0][0], U.e[1][1], -U.e[0][1], U.e[1][0]));
+template <bool IN_TURN = false, typename R> WHMC_DEV void reconstruct_row2(SU3<R>& U) {
+  U.e[2][0] = conj(cdot2<IN_TURN>(U.e[0][1], U.e[1][2], -U.e[0][2], U.e[1][1]));
+  U.e[2][1] = conj(cdot2<IN_TURN>(U.e[0][2], U.e[1][0], -U.e[0][0], U.e[1][2]));
+  U.e[2][2] = conj(cdot2<IN_TURN>(U.e[0][0], U.e[1][1], -U.e[0][1], U.e[1][0]));
 }
 
 // 8 real parameters per link, the form of Clark, Babich, Barros, Brower and Rebbi (Comput. Phys.
@@ -593,7 +604,7 @@ struct LinkF16_12T {
       U.e[(2 * k) / 3][(2 * k) % 3] = {h2f((unsigned short)(v.x & 0xffffu)), h2f((unsigned short)(v.x >> 16))};
       U.e[(2 * k + 1) / 3][(2 * k + 1) % 3] = {h2f((unsigned short)(v.y & 0xffffu)), h2f((unsigned short)(v.y >> 16))};
     }
-    reconstruct_row2(U);
+    reconstruct_row2<true>(U);
   }
 };
 
@@ -650,6 +661,13 @@ template <class L> struct is_8real : std::false_type {};
 template <bool NT> struct is_8real<LinkF64_8T<NT>> : std::true_type {};
 template <bool NT> struct is_8real<LinkF32_8T<NT>> : std::true_type {};
 template <bool NT> struct is_8real<LinkF16_8T<NT>> : std::true_type {};
+
+// Wavefronts per SIMD that the compiler arranges a hop's loads for: three with FP32 18-real links, whose hop has room
+// for the next direction's loads then (130 registers).  Left to itself it takes four and 102, with fewer loads on
+// their way: 32x24^3 on a full spinor 57.3 us against 49.6.
+template <class L> constexpr int hop_waves = 8;
+template <bool NT> constexpr int hop_waves<LinkF32_18T<NT>> = 3;
+#define WHMC_WAVES(L) __attribute__((amdgpu_waves_per_eu(1, hop_waves<L>)))
 
 using LinkF64_18 = LinkF64_18T<false>;
 using LinkF64_12 = LinkF64_12T<false>;

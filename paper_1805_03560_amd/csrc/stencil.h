@@ -75,11 +75,11 @@ WHMC_DEV void hop_apply(const SU3<R>& U, const Spinor<R>& s, R sc, bool wrap, Ha
   project<MU, SGN, SCALED>(s, sc, h);
   if (MU == 0 && wrap) negate(h);
   if (DIR > 0) {
-    mul(U, h.c[0], u.c[0]);
-    mul(U, h.c[1], u.c[1]);
+    mul<SCALED>(U, h.c[0], u.c[0]);
+    mul<SCALED>(U, h.c[1], u.c[1]);
   } else {
-    mul_dag(U, h.c[0], u.c[0]);
-    mul_dag(U, h.c[1], u.c[1]);
+    mul_dag<SCALED>(U, h.c[0], u.c[0]);
+    mul_dag<SCALED>(U, h.c[1], u.c[1]);
   }
 }
 
