@@ -93,9 +93,9 @@ __global__ __launch_bounds__(kBlock) void k_bs_mv(Geom g, Lnk L, SpinorF64 te, S
 template <int MODE>
 __global__ __launch_bounds__(kFinWG) void k_bs_fin(BSScalars* sc, const double* partials, int nb) {
   if (bs_halted(sc)) return;
-  const double a = sum_partials<kFinWG>(partials, nb);
-  const double b = sum_partials<kFinWG>(partials + nb, nb);
-  const double c = MODE == 1 ? sum_partials<kFinWG>(partials + 2 * nb, nb) : 0.0;
+  const double a = sum_partials(partials, nb);
+  const double b = sum_partials(partials + nb, nb);
+  const double c = MODE == 1 ? sum_partials(partials + 2 * nb, nb) : 0.0;
   if (threadIdx.x != 0) return;
   if (MODE == 0) {
     const double den = a * a + b * b;
@@ -176,9 +176,9 @@ __global__ __launch_bounds__(kBlock) void k_bs_update(int Vh, SpinorF64 x, Spino
 // rho' = (rhat, r), |r|^2, beta = (rho' / rho)(alpha / omega), convergence test
 __global__ __launch_bounds__(kFinWG) void k_bs_fin_rho(BSScalars* sc, const double* partials, int nb) {
   if (bs_halted(sc)) return;
-  const double a = sum_partials<kFinWG>(partials, nb);
-  const double b = sum_partials<kFinWG>(partials + nb, nb);
-  const double rr = sum_partials<kFinWG>(partials + 2 * nb, nb);
+  const double a = sum_partials(partials, nb);
+  const double b = sum_partials(partials + nb, nb);
+  const double rr = sum_partials(partials + 2 * nb, nb);
   if (threadIdx.x != 0) return;
   sc->iter += 1;
   sc->rr = rr;
@@ -253,14 +253,14 @@ static void enqueue_bs(whmc_ctx* c, const Lnk& L, SpinorF64 x, SpinorF64 r, Spin
     hipLaunchKernelGGL((k_bs_hop<DAG, Lnk>), gs, blk, c->stencil_lds, c->stream, c->g, L, p, te, sc);
     hipLaunchKernelGGL((k_bs_mv<DAG, 0, Lnk>), gs, blk, c->stencil_lds, c->stream, c->g, L, te, p, v, rhat, k2, sc,
                        red, ns);
-    hipLaunchKernelGGL(k_bs_fin<0>, dim3(1), dim3(kFinWG), 0, c->stream, sc, red.partials, ns);
+    hipLaunchKernelGGL(k_bs_fin<0>, dim3(1), dim3(fin_threads(ns)), 0, c->stream, sc, red.partials, ns);
     hipLaunchKernelGGL(k_bs_s, gv, blk, 0, c->stream, c->Vh, r, v, s, sc);
     hipLaunchKernelGGL((k_bs_hop<DAG, Lnk>), gs, blk, c->stencil_lds, c->stream, c->g, L, s, te, sc);
     hipLaunchKernelGGL((k_bs_mv<DAG, 1, Lnk>), gs, blk, c->stencil_lds, c->stream, c->g, L, te, s, t, s, k2, sc,
                        red, ns);
-    hipLaunchKernelGGL(k_bs_fin<1>, dim3(1), dim3(kFinWG), 0, c->stream, sc, red.partials, ns);
+    hipLaunchKernelGGL(k_bs_fin<1>, dim3(1), dim3(fin_threads(ns)), 0, c->stream, sc, red.partials, ns);
     hipLaunchKernelGGL(k_bs_update, gv, blk, 0, c->stream, c->Vh, x, p, s, t, r, rhat, sc, red, nv);
-    hipLaunchKernelGGL(k_bs_fin_rho, dim3(1), dim3(kFinWG), 0, c->stream, sc, red.partials, nv);
+    hipLaunchKernelGGL(k_bs_fin_rho, dim3(1), dim3(fin_threads(nv)), 0, c->stream, sc, red.partials, nv);
     hipLaunchKernelGGL(k_bs_p, gv, blk, 0, c->stream, c->Vh, p, r, v, sc);
   }
 }

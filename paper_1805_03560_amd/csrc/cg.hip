@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kBlock) WHMC_WAVES(Lnk) void k_cg2(Geom g, Lnk L, S
 // pass 2 of kernel 2: (p, A p) -> alpha
 __global__ __launch_bounds__(kFinWG) void k_cg2_fin(CGScalars* sc, const double* partials, int nb) {
   if (halted(sc)) return;
-  const double pAp = sum_partials<kFinWG>(partials, nb);
+  const double pAp = sum_partials(partials, nb);
   if (threadIdx.x != 0) return;
   sc->pAp = pAp;
   if (pAp > 0.0 && pAp < INFINITY) {
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(kBlock) WHMC_WAVES(Lnk) void k_cg4(Geom g, Lnk L, S
 template <bool MIXED>
 __global__ __launch_bounds__(kFinWG) void k_cg4_fin(CGScalars* sc, const double* partials, int nb) {
   if (halted(sc)) return;
-  const double rr_new = sum_partials<kFinWG>(partials, nb);
+  const double rr_new = sum_partials(partials, nb);
   if (threadIdx.x != 0) return;
   const double rr_old = sc->rr;
   sc->beta = rr_new / rr_old;
@@ -324,11 +324,11 @@ static whmc_status enqueue_iters(whmc_ctx* c, const Lnk& L, S p, S t, S u, S v, 
     TraceRange tr(MIXED ? "whmc cg iteration (mixed)" : "whmc cg iteration");
     hipLaunchKernelGGL((k_cg1<Lnk, S>), grid, block, lds, c->stream, c->g, L, p, t, c->scal);
     hipLaunchKernelGGL((k_cg2<Lnk, S>), grid, block, lds, c->stream, c->g, L, t, p, u, k2, c->scal, c->red);
-    hipLaunchKernelGGL(k_cg2_fin, dim3(1), dim3(kFinWG), 0, c->stream, c->scal, c->red.partials, (int)grid.x);
+    hipLaunchKernelGGL(k_cg2_fin, dim3(1), dim3(fin_threads(grid.x)), 0, c->stream, c->scal, c->red.partials, (int)grid.x);
     hipLaunchKernelGGL((k_cg3<Lnk, S>), grid, block, lds, c->stream, c->g, L, u, v, c->scal);
     hipLaunchKernelGGL((k_cg4<Lnk, S, SR, MIXED>), grid, block, lds, c->stream, c->g, L, v, u, p, r, x, k2, c->scal,
                        c->red);
-    hipLaunchKernelGGL(k_cg4_fin<MIXED>, dim3(1), dim3(kFinWG), 0, c->stream, c->scal, c->red.partials, (int)grid.x);
+    hipLaunchKernelGGL(k_cg4_fin<MIXED>, dim3(1), dim3(fin_threads(grid.x)), 0, c->stream, c->scal, c->red.partials, (int)grid.x);
     hipLaunchKernelGGL((k_cg5<S, SR>), grid, block, 0, c->stream, c->Vh, p, r, c->scal);
   }
   WHMC_HIP(hipGetLastError());

@@ -574,8 +574,12 @@ static int reduce_blocks(whmc_ctx* c, long long n) {
   long long b = (n + kBlock - 1) / kBlock;
   return (int)(b < 1024 ? b : 1024);
 }
+__global__ __launch_bounds__(kFinWG) void k_finish_sum(const double* partials, int n, double* out) {
+  const double t = sum_partials(partials, n);
+  if (threadIdx.x == 0) *out = t;
+}
 whmc_status finish_sum(whmc_ctx* c, int nparts, double* dev_out) {
-  hipLaunchKernelGGL(k_finish_sum<kFinWG>, dim3(1), dim3(kFinWG), 0, c->stream, c->red.partials, nparts, dev_out);
+  hipLaunchKernelGGL(k_finish_sum, dim3(1), dim3(fin_threads(nparts)), 0, c->stream, c->red.partials, nparts, dev_out);
   WHMC_HIP(hipGetLastError());
   return WHMC_OK;
 }

@@ -711,32 +711,34 @@ WHMC_DEV void block_partial(double v, double* partials, int slot) {
   if (threadIdx.x == 0) partials[slot] = s;
 }
 
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_finish_sum(const double* partials, int n, double* out);
+// pass 2 helper: sum of p[0..n) by one workgroup of fin_threads(n) threads in a fixed order; valid in thread 0.
+// Eight loads are on their way at once: a pass is bound by their latency (8192 partials of a 32^3 x 64 hop: 10.5 us
+// with 256 threads and one load each at a time, 4.6 with 1024).  Where 256 threads have them all on their way, more
+// wavefronts only take longer to meet (BiCGstab on 8^4, nine sums an iteration: 2061 us with 256 threads, 2146 with
+// 1024).
+constexpr int kFinWG = 1024;
+inline unsigned fin_threads(int n) { return n <= 8 * 256 ? 256u : (unsigned)kFinWG; }
 
-// pass 2 helper: sum of p[0..n) by one block of BLOCK threads in a fixed order; valid in thread 0.  Eight
-// loads are on their way at once: a pass is bound by their latency (8192 partials of a 32^3 x 64 hop:
-// 10.5 us with 256 threads and one load each at a time, 4.6 so).
-template <int BLOCK>
 WHMC_DEV double sum_partials(const double* p, int n) {
-  __shared__ double lds[BLOCK / 64];
+  __shared__ double lds[kFinWG / 64];
+  const int B = blockDim.x;
   double t = 0.0;
-  for (int k0 = threadIdx.x; k0 < n; k0 += 8 * BLOCK) {
+  for (int k0 = threadIdx.x; k0 < n; k0 += 8 * B) {
     double v[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = k0 + j * BLOCK < n ? p[k0 + j * BLOCK] : 0.0;
+    for (int j = 0; j < 8; ++j) v[j] = k0 + j * B < n ? p[k0 + j * B] : 0.0;
 #pragma unroll
     for (int j = 0; j < 8; ++j) t += v[j];
   }
+  __syncthreads();   // the previous sum is read
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = t;
   __syncthreads();
-  return block_sum<BLOCK>(t, lds);
-}
-constexpr int kFinWG = 1024;   // threads of the one-workgroup kernels that finish a reduction
-
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_finish_sum(const double* partials, int n, double* out) {
-  const double t = sum_partials<BLOCK>(partials, n);
-  if (threadIdx.x == 0) *out = t;
+  double s = 0.0;
+  if (threadIdx.x == 0)
+    for (int w = 0; w < B / 64; ++w) s += lds[w];
+  return s;
 }
 
 }  // namespace whmc

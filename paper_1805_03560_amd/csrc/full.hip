@@ -78,7 +78,7 @@ __global__ __launch_bounds__(kBlock) void k_fullM_update(Geom g, Lnk L, SpinorF6
 
 __global__ __launch_bounds__(kFinWG) void k_full_alpha(CGScalars* sc, const double* partials, int nb) {
   if (full_halted(sc)) return;
-  const double pAp = sum_partials<kFinWG>(partials, nb);
+  const double pAp = sum_partials(partials, nb);
   if (threadIdx.x != 0) return;
   sc->pAp = pAp;
   if (pAp > 0.0 && pAp < INFINITY) {
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kFinWG) void k_full_alpha(CGScalars* sc, const doub
 
 __global__ __launch_bounds__(kFinWG) void k_full_beta(CGScalars* sc, const double* partials, int nb) {
   if (full_halted(sc)) return;
-  const double rr_new = sum_partials<kFinWG>(partials, nb);
+  const double rr_new = sum_partials(partials, nb);
   if (threadIdx.x != 0) return;
   sc->beta = rr_new / sc->rr;
   sc->rr_old = sc->rr;
@@ -217,11 +217,11 @@ static whmc_status cg_full_impl(whmc_ctx* c, const Lnk& L, double* x, const doub
         TraceRange tr("whmc full-lattice cg iteration");
         hipLaunchKernelGGL((k_fullM<0, true, true, Lnk>), grid, block, 0, c->stream, c->g, L, half64(P, Vh, 0),
                            half64(P, Vh, 1), half64(T, Vh, 0), half64(T, Vh, 1), kappa, c->scal, c->red);
-        hipLaunchKernelGGL(k_full_alpha, dim3(1), dim3(kFinWG), 0, c->stream, c->scal, c->red.partials, (int)grid.x);
+        hipLaunchKernelGGL(k_full_alpha, dim3(1), dim3(fin_threads(grid.x)), 0, c->stream, c->scal, c->red.partials, (int)grid.x);
         hipLaunchKernelGGL((k_fullM_update<Lnk>), grid, block, 0, c->stream, c->g, L, half64(T, Vh, 0),
                            half64(T, Vh, 1), half64(P, Vh, 0), half64(P, Vh, 1), half64(R, Vh, 0), half64(R, Vh, 1),
                            half64(x, Vh, 0), half64(x, Vh, 1), kappa, c->scal, c->red);
-        hipLaunchKernelGGL(k_full_beta, dim3(1), dim3(kFinWG), 0, c->stream, c->scal, c->red.partials, (int)grid.x);
+        hipLaunchKernelGGL(k_full_beta, dim3(1), dim3(fin_threads(grid.x)), 0, c->stream, c->scal, c->red.partials, (int)grid.x);
         hipLaunchKernelGGL(k_full_p, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, n, (double2*)P,
                            (const double2*)R, c->scal);
       }

@@ -262,7 +262,7 @@ __global__ __launch_bounds__(kBlock) void k_mcg2(Geom g, int nrhs, int G, int or
 __global__ __launch_bounds__(kFinWG) void k_mcg2_fin(CGScalars* sc, int nrhs, const double* partials, int nb) {
   const int r = blockIdx.x;
   if (!rhs_live(sc, r, nrhs)) return;
-  const double pAp = sum_partials<kFinWG>(partials + (size_t)r * nb, nb);
+  const double pAp = sum_partials(partials + (size_t)r * nb, nb);
   if (threadIdx.x != 0) return;
   sc[r].pAp = pAp;
   if (pAp > 0.0 && pAp < INFINITY) {
@@ -333,7 +333,7 @@ template <bool MIXED>
 __global__ __launch_bounds__(kFinWG) void k_mcg4_fin(CGScalars* sc, int nrhs, const double* partials, int nb) {
   const int r = blockIdx.x;
   if (!rhs_live(sc, r, nrhs)) return;
-  const double rr_new = sum_partials<kFinWG>(partials + (size_t)r * nb, nb);
+  const double rr_new = sum_partials(partials + (size_t)r * nb, nb);
   if (threadIdx.x != 0) return;
   CGScalars& q = sc[r];
   const double rr_old = q.rr;
@@ -383,7 +383,7 @@ __global__ __launch_bounds__(kBlock) void k_mres(Geom g, int nrhs, int G, int or
 __global__ __launch_bounds__(kFinWG) void k_mres_fin(BySet live, const double* partials, int nb, double* out) {
   const int r = blockIdx.x;
   if (!live(r)) return;
-  const double rr = sum_partials<kFinWG>(partials + (size_t)r * nb, nb);
+  const double rr = sum_partials(partials + (size_t)r * nb, nb);
   if (threadIdx.x == 0) out[r] = rr;
 }
 
@@ -711,13 +711,13 @@ static void enqueue_multi(whmc_ctx* c, int nrhs, int order, const Lnk& L, S p, S
     hipLaunchKernelGGL((k_mcg2<NB, R, Lnk, S, ByScalars>), grid, block, 0, c->stream, c->g, nrhs, G, order, L, t, p, u,
                        k2,
                        live, c->red, ns);
-    hipLaunchKernelGGL(k_mcg2_fin, dim3(nrhs), dim3(kFinWG), 0, c->stream, c->scal, nrhs, c->red.partials, ns * R);
+    hipLaunchKernelGGL(k_mcg2_fin, dim3(nrhs), dim3(fin_threads(ns * R)), 0, c->stream, c->scal, nrhs, c->red.partials, ns * R);
     hipLaunchKernelGGL((k_mcg3<NB, R, Lnk, S, ByScalars>), grid, block, 0, c->stream, c->g, G, order, L, u, v, live);
     hipLaunchKernelGGL((k_mcg4<NB, R, Lnk, S, SR, MIXED>), grid, block, 0, c->stream, c->g, nrhs, G, order, L, v, u, p,
                        r, x,
                        k2, c->scal, c->red, ns);
-    hipLaunchKernelGGL(k_mcg4_fin<MIXED>, dim3(nrhs), dim3(kFinWG), 0, c->stream, c->scal, nrhs, c->red.partials,
-                       ns * R);
+    hipLaunchKernelGGL(k_mcg4_fin<MIXED>, dim3(nrhs), dim3(fin_threads(ns * R)), 0, c->stream, c->scal, nrhs,
+                       c->red.partials, ns * R);
     hipLaunchKernelGGL((k_mcg5<S, SR>), grid5, block, 0, c->stream, c->Vh, nrhs, p, r, c->scal);
   }
 }
@@ -734,10 +734,10 @@ static whmc_status enqueue_sweep(whmc_ctx* c, int prec, int links, int nrhs, S p
     TraceRange tr("whmc multi-rhs cg iteration");
     WHMC_TRY(sweep_hop(c, prec, links, 0, 0, nrhs, t.p, p.p, ~0u, c->scal));
     WHMC_TRY(sweep_u(c, prec, links, nrhs, u.p, t.p, p.p, k2.v));
-    hipLaunchKernelGGL(k_mcg2_fin, dim3(nrhs), dim3(kFinWG), 0, c->stream, c->scal, nrhs, part, np);
+    hipLaunchKernelGGL(k_mcg2_fin, dim3(nrhs), dim3(fin_threads(np)), 0, c->stream, c->scal, nrhs, part, np);
     WHMC_TRY(sweep_hop(c, prec, links, 0, 1, nrhs, v.p, u.p, ~0u, c->scal));
     WHMC_TRY(sweep_r(c, prec, links, nrhs, r.p, x.p, v.p, u.p, p.p, k2.v));
-    hipLaunchKernelGGL(k_mcg4_fin<mixed>, dim3(nrhs), dim3(kFinWG), 0, c->stream, c->scal, nrhs, part, np);
+    hipLaunchKernelGGL(k_mcg4_fin<mixed>, dim3(nrhs), dim3(fin_threads(np)), 0, c->stream, c->scal, nrhs, part, np);
     hipLaunchKernelGGL((k_mcg5<S, S>), grid5, block, 0, c->stream, c->Vh, nrhs, p, r, c->scal);
   }
   return WHMC_OK;
@@ -760,7 +760,7 @@ static void enqueue_residual(whmc_ctx* c, unsigned mask, int nrhs, int order, co
   hipLaunchKernelGGL((k_mres<R, Lnk>), grid, block, 0, c->stream, c->g, nrhs, G, order, L, v, u, b, r64, k2, live,
                      c->red,
                      ns);
-  hipLaunchKernelGGL(k_mres_fin, dim3(nrhs), dim3(kFinWG), 0, c->stream, live, c->red.partials, ns * R, rr_dev);
+  hipLaunchKernelGGL(k_mres_fin, dim3(nrhs), dim3(fin_threads(ns * R)), 0, c->stream, live, c->red.partials, ns * R, rr_dev);
 }
 
 static whmc_status residual_multi(whmc_ctx* c, unsigned mask, int nrhs, const double* x, const double* b,
@@ -768,8 +768,8 @@ static whmc_status residual_multi(whmc_ctx* c, unsigned mask, int nrhs, const do
   if (split_hops(c, WHMC_F64, WHMC_L18, nrhs)) return split_residual(c, mask, nrhs, x, b, k2.v, t, u, v, r64, rr_dev);
   if (sweep_rhs(c, WHMC_F64, WHMC_L18, nrhs)) {
     WHMC_TRY(sweep_residual(c, mask, nrhs, x, b, k2.v, t, u, v, r64));
-    hipLaunchKernelGGL(k_mres_fin, dim3(nrhs), dim3(kFinWG), 0, c->stream, BySet{mask, nrhs}, c->red.partials,
-                       sweep_parts(c), rr_dev);
+    hipLaunchKernelGGL(k_mres_fin, dim3(nrhs), dim3(fin_threads(sweep_parts(c))), 0, c->stream, BySet{mask, nrhs},
+                       c->red.partials, sweep_parts(c), rr_dev);
     WHMC_HIP(hipGetLastError());
     return WHMC_OK;
   }

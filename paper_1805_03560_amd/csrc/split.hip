@@ -440,7 +440,7 @@ whmc_status split_fullM(whmc_ctx* c, int dag, int nrhs, double* out, const doubl
 __global__ __launch_bounds__(kFinWG) void k_split_sum(unsigned mask, const double* part, int nb, double* out) {
   const int r = blockIdx.x;
   if (!((mask >> r) & 1u)) return;
-  const double t = sum_partials<kFinWG>(part + (size_t)r * nb, nb);
+  const double t = sum_partials(part + (size_t)r * nb, nb);
   if (threadIdx.x == 0) out[r] = t;
 }
 
@@ -456,7 +456,8 @@ whmc_status split_residual(whmc_ctx* c, unsigned mask, int nrhs, const double* x
   launch_split<0, kCgU>(c, 1, nrhs, L, T, X, U, X, R, R, 0.0, kk, mask, nullptr, pa, pa);
   launch_split<1, kCgHop>(c, 0, nrhs, L, U, U, V, U, R, R, 0.0, kk, mask, nullptr, pa, pa);
   launch_split<1, kRes>(c, 1, nrhs, L, V, U, R, B, R, R, 0.0, kk, mask, nullptr, pa, pa);
-  hipLaunchKernelGGL(k_split_sum, dim3(nrhs), dim3(kFinWG), 0, c->stream, mask, pa, split_blocks(c), rr_dev);
+  hipLaunchKernelGGL(k_split_sum, dim3(nrhs), dim3(fin_threads(split_blocks(c))), 0, c->stream, mask, pa,
+                     split_blocks(c), rr_dev);
   WHMC_HIP(hipGetLastError());
   return WHMC_OK;
 }
