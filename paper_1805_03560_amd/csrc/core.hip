@@ -662,7 +662,7 @@ whmc_status whmc_create(whmc_ctx** out, const int dims[4], int device, void* str
     c->g.nbs = split ? (int)(slice / kBlock) : 0;
     c->g.xq = split ? (c->g.nbs + 7) / 8 : 0;
     const long long plane = (long long)dims[2] * dims[3] / 2;
-    const bool cols = split && dims[1] % 8 == 0 && plane % kBlock == 0 && plane / kBlock >= 2;
+    const bool cols = split && dims[1] % 16 == 0 && plane % kBlock == 0 && plane / kBlock >= 2;
     c->g.nbp = cols ? (int)(plane / kBlock) : 0;
     c->g.zx = cols ? dims[1] / 8 : 0;
     c->g.sched = 0;

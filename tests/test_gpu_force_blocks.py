@@ -13,14 +13,14 @@ from gpu_util import algebra_to_numpy, make_ctx, oracle_cached, pack_half, rel_e
 
 pytestmark = pytest.mark.gpu
 
-# planes of 2, 2 and 4 blocks, 1, 2 and 1 planes per XCD; V_h = 4096 (a wavefront per workgroup), 8192 and 16384
-# (four)
-DIMS = [(2, 8, 16, 32), (2, 16, 32, 16), (4, 8, 32, 32)]
+# planes of 2, 2 and 4 blocks, 2, 4 and 2 planes per XCD
+DIMS = [(2, 16, 16, 32), (2, 32, 32, 16), (2, 16, 32, 32)]
 
 
-# ... and lattices without columns on both sides of that line, with part of a block
-@pytest.mark.parametrize("dims", DIMS + [(6, 2, 6, 6), (16, 8, 8, 8), (18, 6, 6, 14)])
-def test_gauge_force_in_columns(dims):
+# ... and lattices without columns: one plane per XCD, and both sides of V_h = 4096, up to which a workgroup is one
+# wavefront, with part of a block
+@pytest.mark.parametrize("dims", DIMS + [(2, 8, 16, 32), (6, 2, 6, 6), (16, 8, 8, 8), (18, 6, 6, 14)])
+def test_gauge_force_orders(dims):
     U = synth.smooth_links(dims, 9530, width=0.8)
     ctx = make_ctx(dims, U)
     F = ctx.force(None, 0, 0, 0, 0.15, 5.6, flags=whmc.FORCE_GAUGE)
