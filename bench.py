@@ -448,6 +448,7 @@ def multi_rhs(whmc, torch, stream):
             nb, lanes, order, _ = ctx.autotune(p, links, nrhs)
             bp = b if p == whmc.F64 else ctx.convert_spinor(b, whmc.F64, p, nrhs)
             o = ctx.half_spinor(p, nrhs)
+            ctx.apply_H_multi(bp, 0, nrhs, prec=p, links=links, out=o)   # the kernel's first launch loads it
             ms = time_events(lambda: ctx.apply_H_multi(bp, 0, nrhs, prec=p, links=links, out=o), stream, torch, reps=10)
             blocked = time_events(lambda: ctx.apply_H_multi(bp, 0, nrhs, prec=p, links=links, out=o, rhs_block=nb,
                                                             rhs_lanes=lanes, rhs_order=order), stream, torch, reps=10)
